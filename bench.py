@@ -58,7 +58,7 @@ def percentile(xs, q):
 
 
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1209_3332_amd", "csrc", f)
-                  for f in ("kernels.hpp", "component.hpp", "label.hpp", "recon.hip")]
+                  for f in ("kernels.hpp", "region.hpp", "component.hpp", "label.hpp", "recon.hip")]
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "revisit_drain_hbm_traffic.md")
 
 

@@ -137,12 +137,18 @@ typedef struct {
                               the serving loop runs every request at the context's */
 } recon_task;
 
-/* Tuning and capacity knobs; zero fields take the defaults. */
+/* Tuning and capacity knobs; zero fields take the defaults.  With scan_rounds
+ * of at least 1 (the default) a reconstruction runs on the register-resident
+ * kernel, whose regions, sweeps and exchange do not depend on block_rows,
+ * queue_capacity, the number of scan rounds, the drain budgets or the spill
+ * queues: block_rows then only sets the blocks that the statistics and the limit
+ * of recon_dilate_noalloc count.  scan_rounds = -1 and the staged pipelines
+ * (stop_after_stage) run on the queue kernel, which all of them steer. */
 typedef struct {
     int32_t block_rows;        /* rows per work block: 16, 32 or 64 (default 32) */
     int32_t queue_capacity;    /* LDS queue entries per workgroup: a power of two in 64..8192 */
     int32_t scan_rounds;       /* directional pass rounds on a block's first visit,
-                                  1..8; 0 = default (3); -1 = none */
+                                  1..8; 0 = default (3); -1 = none (the queue kernel) */
     int32_t wg_per_cu;         /* cap on resident workgroups per CU (0 = occupancy limit) */
     int64_t serve_mem_cap;     /* serving admission cap in device bytes (default 64 GiB) */
     int32_t serve_slots;       /* serving in-flight task slots (default 256) */

@@ -87,8 +87,8 @@ struct UnitWalk {
     }
 };
 
-// Classification: one wave per block (grid-stride), the block's rows loaded
-// together; each lane keeps the OR and AND of its nonzero mask bytes, the
+// Classification: one wave per block of up to 32 rows, or 32 rows of a higher
+// one (grid-stride), the rows loaded together; each lane keeps the OR and AND of its nonzero mask bytes, the
 // wave combines them once per task it leaves, and only a combination that
 // changes a task's words is written.  A wave skips the blocks of a task whose
 // words already show two different nonzero values (it can never take the
@@ -98,7 +98,9 @@ template <int BH>
 __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
     if (a.work->classify_skip == seq_of(tt)) return;   // the samples decided every route
     const int ln = lane_id();
-    const uint32_t n = total_blocks_of(tt);
+    constexpr int CH = BH < 32 ? BH : 32;   // rows of a unit, their loads in flight together
+    constexpr int PER = BH / CH;
+    const uint32_t n = total_blocks_of(tt) * PER;
     UnitWalk wk;
     int acc_k = -1;                 // task whose partial OR / AND this wave holds
     uint32_t acc_or = 0, acc_and = 0xffu;
@@ -128,7 +130,8 @@ __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
         acc_or = 0;
         acc_and = 0xffu;
     };
-    for (uint32_t gb = blockIdx.x; gb < n; gb += gridDim.x) {
+    for (uint32_t u = blockIdx.x; u < n; u += gridDim.x) {
+        const uint32_t gb = u / PER;
         wk.at(tt, gb);
         const TaskDev &t = wk.t;
         if (!t.lab) continue;
@@ -146,11 +149,12 @@ __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
         const BlockGeom g = geom<BH>(t, lb / t.nbx, lb % t.nbx);
         const int x = g.x0 + 4 * ln;
         const int valid = min(4, g.bw - 4 * ln);
-        uint32_t m[BH];
+        const int r0 = (int)(u % PER) * CH;
+        uint32_t m[CH];
 #pragma unroll
-        for (int r = 0; r < BH; ++r) m[r] = (r < g.bh && valid > 0) ? mask4(t, g.y0 + r, x, valid) : 0u;
+        for (int r = 0; r < CH; ++r) m[r] = (r0 + r < g.bh && valid > 0) ? mask4(t, g.y0 + r0 + r, x, valid) : 0u;
 #pragma unroll
-        for (int r = 0; r < BH; ++r)
+        for (int r = 0; r < CH; ++r)
             for (int j = 0; j < 4; ++j) {
                 const uint32_t b = byte_of(m[r], j);
                 if (b) {

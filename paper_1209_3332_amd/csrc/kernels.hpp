@@ -24,8 +24,10 @@
 //   K2 border_seed    for every block, compare its border with the adjacent
 //                     pixels of its neighbours and request a visit of each
 //                     neighbour that the border can still raise.
-//   K3 revisit_drain  a persistent grid of waves pulls requested blocks from a
-//                     device ring, reloads them with a fresh halo, seeds an
+//   K3 revisit_drain  (the queue kernel: launches whose first visits do not sweep,
+//                     and the staged pipeline; others run region.hpp's kernel on
+//                     the same scheduler) a persistent grid of waves pulls
+//                     requested blocks from a device ring, reloads them with a fresh halo, seeds an
 //                     LDS queue from every pixel a neighbour can raise, drains
 //                     it, writes back the changed rows and requests the
 //                     neighbours its border can still raise.  Per-block state
@@ -101,6 +103,7 @@ struct TaskDev {
     int32_t qcap;          // LDS queue entries (<= the launch's LDS allocation)
     int32_t *lab;          // int32 label plane of the component route (null: the task never takes it)
     int64_t pitch_lab;     // its row pitch in elements (a multiple of 4)
+    int32_t stat_rows;      // rows of the caller's work blocks (the region kernel counts first visits in those)
 };
 
 // Batch header in device memory, in front of a device task table.

@@ -30,6 +30,7 @@
 #include "kernels.hpp"
 #include "label.hpp"
 #include "component.hpp"
+#include "region.hpp"
 #include "distance.hpp"
 
 namespace {
@@ -56,9 +57,14 @@ int fail(int code, const char *fmt, ...) {
 using rk::BatchHdr;
 static_assert(sizeof(BatchHdr) == 64, "header size");
 
-constexpr int kVariants = 3;   // block rows 16, 32, 64
+constexpr int kVariants = 3;   // block rows 16, 32, 64 (the queue kernel, revisit_drain)
+constexpr int kRegionV = kVariants;        // the register-resident kernel, region_drain
+constexpr int kLaunchVariants = kVariants + 1;
 constexpr int kTimingRing = 64; // launches whose timing marks are kept
 constexpr int kBlockRows[kVariants] = {16, 32, 64};
+constexpr int kRegionR = 16, kRegionNW = 8;   // rows per wave, waves per workgroup
+constexpr int kUnitRows[kLaunchVariants] = {16, 32, 64, kRegionR * kRegionNW};   // rows of a scheduled block
+constexpr int kUnitThreads[kLaunchVariants] = {64, 64, 64, 64 * kRegionNW};
 
 int variant_of(int rows) {
     for (int v = 0; v < kVariants; ++v)
@@ -70,7 +76,8 @@ size_t lds_for(int v, int qcap) {
     switch (v) {
         case 0: return rk::lds_bytes<16>(qcap);
         case 1: return rk::lds_bytes<32>(qcap);
-        default: return rk::lds_bytes<64>(qcap);
+        case 2: return rk::lds_bytes<64>(qcap);
+        default: return rk::region_lds_bytes<kRegionR, kRegionNW>();
     }
 }
 
@@ -78,7 +85,8 @@ const void *drain_fn(int v) {
     switch (v) {
         case 0: return reinterpret_cast<const void *>(&rk::revisit_drain<16>);
         case 1: return reinterpret_cast<const void *>(&rk::revisit_drain<32>);
-        default: return reinterpret_cast<const void *>(&rk::revisit_drain<64>);
+        case 2: return reinterpret_cast<const void *>(&rk::revisit_drain<64>);
+        default: return reinterpret_cast<const void *>(&rk::region_drain<kRegionR, kRegionNW>);
     }
 }
 
@@ -154,17 +162,17 @@ struct recon_ctx {
     rk::Work *last_work = nullptr;      // the counters of the last launch (context or fixed workspace)
     uint8_t *noalloc = nullptr;         // this device's fixed workspace (recon_dilate_noalloc)
     bool last_was_graph = false;   // the last launch replayed a graph (only its total is timed)
-    int resident[kVariants] = {0, 0, 0};
+    int resident[kLaunchVariants] = {};
     // captured batch graphs per variant
     hipStream_t cap_stream = nullptr;
     // the component route's labelling kernels run on a second stream beside
     // the revisit kernel (fork and join events, also inside captured graphs)
     hipStream_t aux_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    hipGraphExec_t graph[kVariants] = {nullptr, nullptr, nullptr};
-    size_t graph_cap_blocks[kVariants] = {0, 0, 0};
-    size_t graph_cap_tasks[kVariants] = {0, 0, 0};
-    size_t graph_cap_scratch[kVariants] = {0, 0, 0};
+    hipGraphExec_t graph[kLaunchVariants] = {};
+    size_t graph_cap_blocks[kLaunchVariants] = {};
+    size_t graph_cap_tasks[kLaunchVariants] = {};
+    size_t graph_cap_scratch[kLaunchVariants] = {};
     // serving (created on the first recon_submit)
     struct Serve;
     Serve *serve = nullptr;
@@ -211,7 +219,7 @@ size_t ring_slots(size_t n_blocks) { return n_blocks + rk::MAX_DRAIN_GRID + 1; }
 int resident_wgs(recon_ctx *c, int v) {
     if (c->resident[v] == 0) {
         int per_cu = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, drain_fn(v), 64,
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, drain_fn(v), kUnitThreads[v],
                                                                     lds_for(v, c->cfg.queue_capacity));
         if (e != hipSuccess || per_cu <= 0) per_cu = 1;
         if (c->cfg.wg_per_cu > 0) per_cu = std::min(per_cu, c->cfg.wg_per_cu);
@@ -239,7 +247,7 @@ void free_workspace(recon_ctx *c) {
 }
 
 void drop_graphs(recon_ctx *c) {
-    for (int v = 0; v < kVariants; ++v) {
+    for (int v = 0; v < kLaunchVariants; ++v) {
         if (c->graph[v]) (void)hipGraphExecDestroy(c->graph[v]);
         c->graph[v] = nullptr;
         c->graph_cap_blocks[v] = c->graph_cap_tasks[v] = c->graph_cap_scratch[v] = 0;
@@ -389,6 +397,7 @@ void build_table(const recon_config &cfg, const recon_task *tasks, int n, int bh
             d.aligned = aligned4(d.i, d.pitch_i);
             uses_scratch[k] = 1;
         }
+        d.stat_rows = t.block_rows ? t.block_rows : cfg.block_rows;
         if (t.op != RECON_OP_DILATE) any_mapped = true;
         d.lab = nullptr;
         d.pitch_lab = (int64_t)round_up((size_t)d.w, 4);
@@ -477,7 +486,7 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         // the component route: classify every task's mask (unless the samples
         // reset_work took already decided every route), then label and
         // reconstruct the two-valued ones (the others' waves exit at once)
-        const int bh = kBlockRows[v];
+        const int bh = kUnitRows[v];
         const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * bh, 4096));
         const int g_tiles = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::LT_H), 4096));
         const size_t lds_lab = (size_t)rk::LT_H * rk::LT_W * sizeof(uint32_t);
@@ -485,9 +494,10 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     switch (v) {                                                                                  \
         case 0: hipLaunchKernelGGL(rk::K<16>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
         case 1: hipLaunchKernelGGL(rk::K<32>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
-        default: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;     \
+        case 2: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
+        default: hipLaunchKernelGGL(rk::K<kUnitRows[kRegionV]>, dim3(GRID), dim3(64), LDS, s, tt, ka); break; \
     }
-        RK_COMP(comp_classify, (int)std::max<uint32_t>(1u, std::min<uint32_t>(nblk, 1024u)), 0);
+        RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 0);
         // A large batch (a replayed graph) forks: the ring and marker planes
         // (prepare) and the revisit kernel of the tasks that keep the block
         // route go to the second stream, while the route's labelling and
@@ -525,7 +535,10 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     if (timing && !merged) HIP_TRY(hipEventRecord(tev[1], d));
     if (stop >= 2) RK_LAUNCH(border_seed, grid12);
     if (timing) HIP_TRY(hipEventRecord(tev[2], d));
-    if (merged || stop >= 3) RK_LAUNCH(revisit_drain, grid3);
+    if (v == kRegionV)
+        hipLaunchKernelGGL((rk::region_drain<kRegionR, kRegionNW>), dim3(grid3), dim3(kUnitThreads[v]), lds, d, tt, ka);
+    else if (merged || stop >= 3)
+        RK_LAUNCH(revisit_drain, grid3);
     if (timing) HIP_TRY(hipEventRecord(tev[3], d));
 #undef RK_LAUNCH
     if (d != s) {   // join the block route's stream
@@ -538,14 +551,26 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     return RECON_OK;
 }
 
+// The launch variant of a list of tasks: the register-resident kernel wherever
+// first visits sweep (scan_rounds of every task at least 1, the default); a
+// caller that asks for none gets the queue kernel, and so do the staged test
+// hooks, whose stages are that kernel's.
+int launch_variant(const recon_config &cfg, const recon_task *tasks, int n) {
+    if (cfg.stop_after_stage != 0) return variant_of(cfg.block_rows);
+    for (int k = 0; k < n; ++k)
+        if (tasks[k].scan_rounds < 0 || (tasks[k].scan_rounds == 0 && cfg.scan_rounds == 0))
+            return variant_of(cfg.block_rows);
+    return kRegionV;
+}
+
 // Enqueue one launch sequence for `tasks` on `stream`.  use_graph replays the
 // context's captured graph for the block shape (the task table then always
 // lives in device memory).
 int run_tasks(recon_ctx *c, const recon_task *tasks, int n, hipStream_t stream, bool use_graph) {
     int rc = ensure_device(c);
     if (rc) return rc;
-    const int bh = c->cfg.block_rows;
-    const int v = variant_of(bh);
+    const int v = launch_variant(c->cfg, tasks, n);
+    const int bh = kUnitRows[v];
     std::vector<rk::TaskDev> table;
     std::vector<char> uses_scratch;
     std::vector<size_t> lab_off;
@@ -1116,7 +1141,9 @@ int recon_dilate_noalloc(recon_ctx *ctx, recon_image *marker, const recon_image 
     size_t scratch_bytes = 0;
     bool any_mapped = false;
     std::vector<size_t> lab_off;
-    build_table(ctx->cfg, &t, 1, bh, table, uses_scratch, total_blocks, scratch_bytes, any_mapped, false, lab_off);
+    const int v = launch_variant(ctx->cfg, &t, 1);   // (a region has at least block_rows rows: never more of them)
+    build_table(ctx->cfg, &t, 1, kUnitRows[v], table, uses_scratch, total_blocks, scratch_bytes, any_mapped, false,
+                lab_off);
     uint8_t *base = ctx->noalloc;
     Workspace ws;
     ws.work = (rk::Work *)base;
@@ -1137,7 +1164,7 @@ int recon_dilate_noalloc(recon_ctx *ctx, recon_image *marker, const recon_image 
     tt.seq_inline = ctx->launch_seq;
     tt.inl[0] = table[0];
     const hipStream_t s = (hipStream_t)stream;
-    rc = enqueue_kernels(ctx, ws, variant_of(bh), tt, total_blocks, 1u, false, false, false, s);
+    rc = enqueue_kernels(ctx, ws, v, tt, total_blocks, 1u, false, false, false, s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(ctx->last_done, s));
     ctx->have_last = true;
@@ -1439,7 +1466,7 @@ int recon_batch(recon_ctx *ctx, const recon_task *tasks, int32_t n, void *stream
     unsigned shapes = 0;
     for (int k = 0; k < n; ++k)
         shapes |= 1u << (tasks[k].block_rows ? variant_of(tasks[k].block_rows) : v_ctx);
-    if (shapes == (1u << v_ctx)) {
+    if (shapes == (1u << v_ctx) || launch_variant(ctx->cfg, tasks, n) == kRegionV) {
         // a batch that fits the kernel arguments is launched directly (its table
         // travels inline: no table copy, and fewer packets than a graph replay,
         // which on this runtime costs more than the launches it saves); larger

@@ -35,7 +35,7 @@ SCAN_ROUNDS = (-1, 1, 2, 3, 4)   # -1: no sweep on first visits (seed and queue 
 BUCKETS = (("small", 1 << 20, 768), ("medium", 6 << 20, 2048), ("large", 1 << 62, 4096))
 
 
-KERNEL_SOURCES = ("kernels.hpp", "component.hpp", "label.hpp", "recon.hip")
+KERNEL_SOURCES = ("kernels.hpp", "region.hpp", "component.hpp", "label.hpp", "recon.hip")
 
 
 def kernel_sha() -> str:

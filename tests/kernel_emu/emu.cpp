@@ -4,16 +4,19 @@
 // hip/hip_runtime.h next to this file and runs the same launch sequence as the
 // library (reset -> fill init -> persistent kernel -> fill finish) on host
 // memory.  Each workgroup (one 64-lane wave) runs on its own OS thread, its
-// lanes as fibers switched at every cross-lane operation, so inter-wave
+// lanes as fibers switched at every cross-lane operation (a workgroup of
+// several waves: one thread per wave, sharing the LDS and a barrier), so inter-wave
 // atomics and the block scheduler run with real concurrency.  Every LDS
 // buffer and every image copy is an exact-size heap allocation, so a build
 // with -fsanitize=address bounds-checks all of the kernels' memory accesses.
 #include "hip/hip_runtime.h"
 
 
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -22,6 +25,7 @@
 #include "../../paper_1209_3332_amd/csrc/label.hpp"
 #include "../../paper_1209_3332_amd/csrc/component.hpp"
 #include "../../paper_1209_3332_amd/csrc/distance.hpp"
+#include "../../paper_1209_3332_amd/csrc/region.hpp"
 
 #if defined(__has_feature)
 #if __has_feature(address_sanitizer)
@@ -65,7 +69,31 @@ kemu_switch:
 constexpr int kLanes = 64;
 constexpr size_t kStack = 512 * 1024;
 
+// A workgroup of several waves: their common LDS and barrier.
+struct Workgroup {
+    int waves = 1;
+    std::vector<uint8_t> lds;
+    std::mutex mu;
+    std::condition_variable cv;
+    int arrived = 0;
+    unsigned generation = 0;
+    void barrier() {
+        std::unique_lock<std::mutex> lk(mu);
+        const unsigned g = generation;
+        if (++arrived == waves) {
+            arrived = 0;
+            ++generation;
+            cv.notify_all();
+        } else {
+            cv.wait(lk, [&] { return generation != g; });
+        }
+    }
+};
+
 struct Wave {
+    Workgroup *wg = nullptr;      // null: the wave is a workgroup of its own
+    int index = 0;                // in its workgroup
+    bool at_barrier = false;      // the lanes are at a workgroup barrier
     void *sched_sp = nullptr;
     void *sp[kLanes] = {};
     std::vector<char *> stacks;
@@ -88,7 +116,7 @@ int lane() { return tw->cur; }
 // The lanes of an emulated wave share one OS thread, so a thread_local index
 // cannot tell them apart: inside a wave the thread index is the lane.
 Dim3 thread_idx() {
-    if (tw) return Dim3{(uint32_t)tw->cur, 0, 0};
+    if (tw) return Dim3{(uint32_t)(tw->index * kLanes + tw->cur), 0, 0};
     return threadIdx_;
 }
 uint8_t *wave_lds() { return tw->lds; }
@@ -120,6 +148,13 @@ static void yield_to_sched() {
 }
 
 void wave_sync() { yield_to_sched(); }
+
+// Workgroup barrier: every lane of the wave stops here; the wave's thread then
+// waits for the workgroup's other waves before the lanes go on.
+void wg_sync() {
+    tw->at_barrier = true;
+    yield_to_sched();
+}
 
 uint64_t exchange(uint64_t v, int src) {
     Wave *w = tw;
@@ -164,12 +199,14 @@ uint64_t ballot(bool pred) {
 }
 
 // Run `body` as one 64-lane wave on the calling thread.
-static bool run_wave(const std::function<void()> &body, size_t lds_size) {
+static bool run_wave(const std::function<void()> &body, size_t lds_size, Workgroup *wg = nullptr, int index = 0) {
     Wave w;
     w.body = body;
+    w.wg = wg;
+    w.index = index;
     w.lds_size = lds_size;
-    w.lds = (uint8_t *)std::malloc(lds_size);
-    std::memset(w.lds, 0xcd, lds_size);   // garbage, like fresh LDS
+    w.lds = wg ? wg->lds.data() : (uint8_t *)std::malloc(lds_size);
+    if (!wg) std::memset(w.lds, 0xcd, lds_size);   // garbage, like fresh LDS
     tw = &w;
     for (int l = 0; l < kLanes; ++l) {
         char *st = (char *)std::malloc(kStack);
@@ -197,6 +234,10 @@ static bool run_wave(const std::function<void()> &body, size_t lds_size) {
             if (!w.finished[l]) ++alive;
         }
         if (alive == 0) break;
+        if (w.at_barrier) {
+            w.at_barrier = false;
+            if (wg) wg->barrier();
+        }
         if (done > 0 && alive > 0) {   // some lanes returned while others wait at a collective
             std::fprintf(stderr, "kemu: non-uniform exit of a wave\n");
             ok = false;
@@ -204,7 +245,7 @@ static bool run_wave(const std::function<void()> &body, size_t lds_size) {
         }
     }
     for (char *st : w.stacks) std::free(st);
-    std::free(w.lds);
+    if (!wg) std::free(w.lds);
     tw = nullptr;
     return ok;
 }
@@ -379,7 +420,10 @@ struct EmuStats {
 int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int n_waves,
             double watchdog_s, int stop_after, EmuStats *stats) {
     using namespace rk;
-    if (bh != 16 && bh != 32 && bh != 64) return -1;
+    // bh 128 and 8: the region kernel with regions of 8 x 16 (as launched) and 2 x 4 rows
+    const bool region = bh == 128 || bh == 8;
+    const int region_waves = bh == 128 ? 8 : 2;
+    if (bh != 16 && bh != 32 && bh != 64 && !region) return -1;
     // exact-size copies so that the sanitizer bounds-checks global accesses
     std::vector<uint8_t *> jplanes(n), iplanes(n, nullptr), scratch(n, nullptr);
     // the component route (KEMU_COMPONENT=1): an exact-size int32 label plane per task
@@ -404,6 +448,7 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
         total += (uint32_t)(d.nby * d.nbx);
         d.scan_rounds = scan_rounds;
         d.qcap = qcap;
+        d.stat_rows = 16;
         jplanes[k] = (uint8_t *)std::malloc(px);
         std::memcpy(jplanes[k], e.image, px);
         d.minv = (e.op == 1 || e.op == 2) ? 1 : 0;
@@ -561,6 +606,7 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
     switch (bh) {                                               \
         case 16: body = [&] { K<16>(tt, ka); }; break;          \
         case 32: body = [&] { K<32>(tt, ka); }; break;          \
+        case 128: body = [&] { K<128>(tt, ka); }; break;        \
         default: body = [&] { K<64>(tt, ka); }; break;          \
     }
                     if (which == 0) { KEMU_PICK(comp_classify) }
@@ -585,7 +631,30 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
     }
     if (!merged) run_grid(1, n_waves);
     if (stop_after >= 2) run_grid(2, n_waves);
-    if (merged || stop_after >= 3) run_grid(3, n_waves);
+    if (region) {   // the region kernel: n_waves workgroups, a thread per wave
+        const size_t words = bh == 128 ? region_lds_bytes<16, 8>() : region_lds_bytes<4, 2>();
+        std::vector<std::unique_ptr<kemu::Workgroup>> wgs;
+        std::vector<std::thread> th;
+        for (int g = 0; g < n_waves; ++g) {
+            wgs.emplace_back(new kemu::Workgroup());
+            kemu::Workgroup *wg = wgs.back().get();
+            wg->waves = region_waves;
+            wg->lds.assign(words, 0xcd);
+            for (int v = 0; v < region_waves; ++v)
+                th.emplace_back([&, g, v, wg] {
+                    kemu::blockIdx_.x = (uint32_t)g;
+                    kemu::gridDim_.x = (uint32_t)n_waves;
+                    kemu::blockDim_.x = (uint32_t)(64 * region_waves);
+                    std::function<void()> body;
+                    if (bh == 128) body = [&] { region_drain<16, 8>(tt, ka); };
+                    else body = [&] { region_drain<4, 2>(tt, ka); };
+                    if (!kemu::run_wave(body, words, wg, v)) bad++;
+                });
+        }
+        for (auto &t : th) t.join();
+    } else if (merged || stop_after >= 3) {
+        run_grid(3, n_waves);
+    }
     if (any_mapped) grid_run([&] { finish_result(tt, route); }, 4, 64);
 
     for (int k = 0; k < n; ++k) {

@@ -18,7 +18,7 @@
 // one wave, whose lanes are fibers of one OS thread)
 #define __shared__ static thread_local
 #define __forceinline__
-#define __launch_bounds__(x)
+#define __launch_bounds__(...)
 #define __align__(x) __attribute__((aligned(x)))
 
 #define __HIP_MEMORY_SCOPE_WAVEFRONT 2
@@ -63,6 +63,7 @@ extern thread_local Dim3 blockIdx_, threadIdx_, blockDim_, gridDim_;
 int lane();                           // current lane of the running wave
 Dim3 thread_idx();                    // inside a wave: (lane, 0, 0); else threadIdx_
 void wave_sync();                     // all 64 lanes reach this point
+void wg_sync();                       // all lanes of the workgroup's waves do
 uint64_t exchange(uint64_t v, int src_lane);   // value of `v` in lane src_lane
 uint64_t ballot(bool p);
 uint8_t *wave_lds();
@@ -77,7 +78,7 @@ void check_lds(const void *p, size_t n);       // bounds check of an LDS access
 #define gridDim kemu::gridDim_
 
 inline int __lane_id() { return kemu::lane(); }
-inline void __syncthreads() { kemu::wave_sync(); }
+inline void __syncthreads() { kemu::wg_sync(); }
 
 // The wave barrier orders memory accesses across the lanes of one wave (the
 // hardware runs them in lockstep); here it is a switch point like a barrier.
@@ -160,6 +161,8 @@ inline uint32_t max(uint32_t a, uint32_t b) { return a > b ? a : b; }
 #define RK_LDS
 #define RK_GLOBAL
 #define RK_LANE_SYNC() kemu::wave_sync()
+#define RK_OPAQUE_S(v) ((void)0)
+#define RK_OPAQUE_V(v) ((void)0)
 namespace rk {
 inline uint8_t *dyn_lds() { return kemu::wave_lds(); }
 }
