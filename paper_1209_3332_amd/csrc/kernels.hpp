@@ -1953,38 +1953,46 @@ __device__ void decide_tasks(const TaskTable &tt, const KArgs &a) {
     const uint32_t n_tasks = n_tasks_of(tt), seq = seq_of(tt);
     const int ln = lane_id();
     const bool grey_work = __hip_atomic_load(&a.work->has_grey, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == seq;
-    // the ring ranges follow task order: an exclusive prefix sum of the
-    // block counts of the tasks that keep the block route (one wave, 64 tasks
-    // per step; `base` carries the sum of the steps before)
+    // the ring ranges: an exclusive prefix sum of the block counts of the tasks
+    // that keep the block route (one wave, 64 tasks per step; `base` carries the
+    // sum of the steps before), the tasks whose mask looks two-valued first.
+    // Most of their blocks have nothing to do before a flood reaches them, so
+    // their first visits are short, and the flood, a chain of visits, starts
+    // beside the other tasks' work instead of after it.
     uint32_t base = 0;
     bool any_route = false;
-    for (uint32_t i0 = 0; i0 < n_tasks; i0 += LANES) {
-        const uint32_t i = i0 + (uint32_t)ln;
-        uint32_t nb = 0;
-        bool take = false;
-        if (i < n_tasks) {
-            const TaskDev t = task_of(tt, (int)i);
-            uint32_t *rw = a.route + ROUTE_WORDS * i;
-            const uint32_t o = __hip_atomic_load(rw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t an = __hip_atomic_load(rw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t thin = __hip_atomic_load(rw + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            take = t.lab && (o == 0u || o == an) && (a.route_policy == 1 || !grey_work || thin != 0u);
-            rw[3] = take ? 1u : 0u;
-            if (take) a.tile_done[i] = 1u;
-            else nb = (uint32_t)(t.nby * t.nbx);
+    for (int pass = 0; pass < 2; ++pass)
+        for (uint32_t i0 = 0; i0 < n_tasks; i0 += LANES) {
+            const uint32_t i = i0 + (uint32_t)ln;
+            uint32_t nb = 0;
+            bool take = false, mine = false;
+            if (i < n_tasks) {
+                const TaskDev t = task_of(tt, (int)i);
+                uint32_t *rw = a.route + ROUTE_WORDS * i;
+                const uint32_t o = __hip_atomic_load(rw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t an = __hip_atomic_load(rw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t thin = __hip_atomic_load(rw + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool two = o == 0u || o == an;
+                take = t.lab && two && (a.route_policy == 1 || !grey_work || thin != 0u);
+                mine = two == (pass == 0);
+                if (mine) {
+                    rw[3] = take ? 1u : 0u;
+                    if (take) a.tile_done[i] = 1u;
+                    else nb = (uint32_t)(t.nby * t.nbx);
+                }
+            }
+            uint32_t incl = nb;   // inclusive prefix sum over the wave
+            for (int d = 1; d < LANES; d <<= 1) {
+                const uint32_t o = __shfl_up(incl, (unsigned)d);
+                if (ln >= d) incl += o;
+            }
+            if (mine && !take) {
+                a.route[ROUTE_WORDS * i + 2] = base + incl - nb;
+                a.tile_pending[i] = nb;
+            }
+            base += __shfl(incl, LANES - 1);
+            any_route |= __ballot(take) != 0ull;
         }
-        uint32_t incl = nb;   // inclusive prefix sum over the wave
-        for (int d = 1; d < LANES; d <<= 1) {
-            const uint32_t o = __shfl_up(incl, (unsigned)d);
-            if (ln >= d) incl += o;
-        }
-        if (i < n_tasks && !take) {
-            a.route[ROUTE_WORDS * i + 2] = base + incl - nb;
-            a.tile_pending[i] = nb;
-        }
-        base += __shfl(incl, LANES - 1);
-        any_route |= __ballot(take) != 0ull;
-    }
     if (ln == 0) {
         a.work->ring_tail = base;
         a.work->pending = base;

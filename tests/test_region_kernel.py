@@ -46,11 +46,14 @@ def test_emulated(emu_exe, oracle_mod, rows, conn):
               {"op": "hdome", "img": grey, "h": 30, "conn": conn},
               {"op": "regional_max", "img": grey, "conn": conn},
               {"op": "fill_holes", "img": np.where(rng.random((40, 300)) < 0.6, 255, 0).astype(np.uint8), "conn": conn}]
-    rc, outs, log = kemu.run(emu_exe, tasks, bh=rows, n_waves=2)
-    assert rc == 0, log[-2000:]
-    assert "ERROR: AddressSanitizer" not in log and "runtime error" not in log, log[-2000:]
-    for i, (t, got) in enumerate(zip(tasks, outs)):
-        assert np.array_equal(got, oracle_mod.run_task(t)), "task %d (%s)" % (i, t["op"])
+    # 2 workgroups for all regions (taken from the ring), and one task with a
+    # workgroup for each of its regions (which waits for its region's requests)
+    for some, n_wg in ((tasks, 2), (tasks[12:13] if rows == 8 else tasks[-7:-6], 12)):
+        rc, outs, log = kemu.run(emu_exe, some, bh=rows, n_waves=n_wg)
+        assert rc == 0, log[-2000:]
+        assert "ERROR: AddressSanitizer" not in log and "runtime error" not in log, log[-2000:]
+        for i, (t, got) in enumerate(zip(some, outs)):
+            assert np.array_equal(got, oracle_mod.run_task(t)), "task %d (%s)" % (i, t["op"])
 
 
 def test_emulated_failed_claims(emu_exe):
