@@ -58,13 +58,16 @@ using rk::BatchHdr;
 static_assert(sizeof(BatchHdr) == 64, "header size");
 
 constexpr int kVariants = 3;   // block rows 16, 32, 64 (the queue kernel, revisit_drain)
-constexpr int kRegionV = kVariants;        // the register-resident kernel, region_drain
-constexpr int kLaunchVariants = kVariants + 1;
+// The register-resident kernel, region_drain, in two shapes: strips of 16 rows in
+// regions of 128, and of 8 rows in regions of 64 for launches that leave most of
+// the chip idle either way (launch_variant).
+constexpr int kRegionV = kVariants, kRegionSmallV = kVariants + 1;
+constexpr int kLaunchVariants = kVariants + 2;
 constexpr int kTimingRing = 64; // launches whose timing marks are kept
 constexpr int kBlockRows[kVariants] = {16, 32, 64};
-constexpr int kRegionR = 16, kRegionNW = 8;   // rows per wave, waves per workgroup
-constexpr int kUnitRows[kLaunchVariants] = {16, 32, 64, kRegionR * kRegionNW};   // rows of a scheduled block
-constexpr int kUnitThreads[kLaunchVariants] = {64, 64, 64, 64 * kRegionNW};
+constexpr int kRegionNW = 8;   // waves per workgroup
+constexpr int kUnitRows[kLaunchVariants] = {16, 32, 64, 16 * kRegionNW, 8 * kRegionNW};   // rows of a scheduled block
+constexpr int kUnitThreads[kLaunchVariants] = {64, 64, 64, 64 * kRegionNW, 64 * kRegionNW};
 
 int variant_of(int rows) {
     for (int v = 0; v < kVariants; ++v)
@@ -77,7 +80,8 @@ size_t lds_for(int v, int qcap) {
         case 0: return rk::lds_bytes<16>(qcap);
         case 1: return rk::lds_bytes<32>(qcap);
         case 2: return rk::lds_bytes<64>(qcap);
-        default: return rk::region_lds_bytes<kRegionR, kRegionNW>();
+        case kRegionV: return rk::region_lds_bytes<16, kRegionNW>();
+        default: return rk::region_lds_bytes<8, kRegionNW>();
     }
 }
 
@@ -86,7 +90,8 @@ const void *drain_fn(int v) {
         case 0: return reinterpret_cast<const void *>(&rk::revisit_drain<16>);
         case 1: return reinterpret_cast<const void *>(&rk::revisit_drain<32>);
         case 2: return reinterpret_cast<const void *>(&rk::revisit_drain<64>);
-        default: return reinterpret_cast<const void *>(&rk::region_drain<kRegionR, kRegionNW>);
+        case kRegionV: return reinterpret_cast<const void *>(&rk::region_drain<16, kRegionNW>);
+        default: return reinterpret_cast<const void *>(&rk::region_drain<8, kRegionNW>);
     }
 }
 
@@ -494,7 +499,8 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     switch (v) {                                                                                  \
         case 0: hipLaunchKernelGGL(rk::K<16>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
         case 1: hipLaunchKernelGGL(rk::K<32>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
-        case 2: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
+        case 2:                                                                                   \
+        case kRegionSmallV: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(64), LDS, s, tt, ka); break; \
         default: hipLaunchKernelGGL(rk::K<kUnitRows[kRegionV]>, dim3(GRID), dim3(64), LDS, s, tt, ka); break; \
     }
         RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 0);
@@ -536,7 +542,9 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     if (stop >= 2) RK_LAUNCH(border_seed, grid12);
     if (timing) HIP_TRY(hipEventRecord(tev[2], d));
     if (v == kRegionV)
-        hipLaunchKernelGGL((rk::region_drain<kRegionR, kRegionNW>), dim3(grid3), dim3(kUnitThreads[v]), lds, d, tt, ka);
+        hipLaunchKernelGGL((rk::region_drain<16, kRegionNW>), dim3(grid3), dim3(kUnitThreads[v]), lds, d, tt, ka);
+    else if (v == kRegionSmallV)
+        hipLaunchKernelGGL((rk::region_drain<8, kRegionNW>), dim3(grid3), dim3(kUnitThreads[v]), lds, d, tt, ka);
     else if (merged || stop >= 3)
         RK_LAUNCH(revisit_drain, grid3);
     if (timing) HIP_TRY(hipEventRecord(tev[3], d));
@@ -551,6 +559,15 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
     return RECON_OK;
 }
 
+// Up to this many regions of 64 rows (one per compute unit) a launch runs on
+// them: half the rows per wave, so a sweep pair takes half the time, and a
+// workgroup alone on its unit keeps every SIMD at two waves.  512 x 512 tile (16
+// regions) 143 -> 119 us against regions of 128 rows, 1531 x 2053 (216) 131 ->
+// 107, 61 x 150 (1) 83 -> 76; 4096 x 4096 (1024) 347 -> 385, the other way: its
+// units are full either way and smaller regions trade borders more often.
+// (Strips of 4 rows, or regions of 32 rows, lose everywhere.)
+constexpr uint64_t kSmallRegions = 256;
+
 // The launch variant of a list of tasks: the register-resident kernel wherever
 // first visits sweep (scan_rounds of every task at least 1, the default); a
 // caller that asks for none gets the queue kernel, and so do the staged test
@@ -560,7 +577,9 @@ int launch_variant(const recon_config &cfg, const recon_task *tasks, int n) {
     for (int k = 0; k < n; ++k)
         if (tasks[k].scan_rounds < 0 || (tasks[k].scan_rounds == 0 && cfg.scan_rounds == 0))
             return variant_of(cfg.block_rows);
-    return kRegionV;
+    uint64_t small = 0;
+    for (int k = 0; k < n; ++k) small += (uint64_t)((tasks[k].image.height + 63) / 64) * ((tasks[k].image.width + 255) / 256);
+    return small <= kSmallRegions ? kRegionSmallV : kRegionV;
 }
 
 // Enqueue one launch sequence for `tasks` on `stream`.  use_graph replays the
@@ -1466,7 +1485,7 @@ int recon_batch(recon_ctx *ctx, const recon_task *tasks, int32_t n, void *stream
     unsigned shapes = 0;
     for (int k = 0; k < n; ++k)
         shapes |= 1u << (tasks[k].block_rows ? variant_of(tasks[k].block_rows) : v_ctx);
-    if (shapes == (1u << v_ctx) || launch_variant(ctx->cfg, tasks, n) == kRegionV) {
+    if (shapes == (1u << v_ctx) || launch_variant(ctx->cfg, tasks, n) >= kRegionV) {
         // a batch that fits the kernel arguments is launched directly (its table
         // travels inline: no table copy, and fewer packets than a graph replay,
         // which on this runtime costs more than the launches it saves); larger

@@ -1,6 +1,6 @@
 """The register-resident revisit kernel (csrc/region.hpp) against the oracle, at
-the sizes where it can go wrong: the edges of a region (128 rows x 256 columns as
-launched, 16 rows per wave), single rows and columns, rows that are not dword
+the sizes where it can go wrong: the edges of a region (128 or 64 rows x 256 columns
+as launched, 16 or 8 rows per wave), single rows and columns, rows that are not dword
 aligned, long corridors, and the knobs that still choose the queue kernel."""
 import numpy as np
 import pytest
@@ -8,8 +8,10 @@ import pytest
 import kemu
 import synth
 
-# region edges in both directions, strip edges (multiples of 16), ragged widths
-SHAPES = [(1, 1), (1, 700), (300, 1), (16, 256), (17, 255), (127, 256), (128, 257), (129, 260), (256, 512), (257, 511)]
+# region edges in both directions, strip edges, ragged widths; the last two are
+# above the 256 regions of 64 rows up to which a launch runs on those
+SHAPES = [(1, 1), (1, 700), (300, 1), (8, 256), (17, 255), (63, 256), (64, 257), (65, 260), (129, 512), (257, 511),
+          (8192, 260), (8193, 511)]
 
 
 def _pairs(rng, h, w):
