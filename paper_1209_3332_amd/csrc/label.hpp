@@ -120,18 +120,30 @@ __device__ __forceinline__ void lds_union(RK_LDS uint32_t *par, uint32_t a, uint
 // grandparent (an atomic minimum: a parent always has the smaller id, so the
 // entry only moves up its own tree, whatever other waves write meanwhile).
 // Without it, a component spanning many tiles (a background, a corridor)
-// builds chains as long as the tiles it crosses, each step a round trip to
-// the device-coherent level.
+// builds chains as long as the tiles it crosses.  The loads are ordinary ones:
+// an entry only ever moves up its tree, so a copy that a cache holds from before
+// still names an ancestor, and the find ends at a node that is, or was, a root
+// (g_union's minimum settles which; a load at the device-coherent level costs a
+// trip to memory for every step).
 __device__ __forceinline__ int32_t g_find(int32_t *lab, int32_t a) {
+    const RK_GLOBAL int32_t *l = (const RK_GLOBAL int32_t *)lab;
     while (true) {
-        const int32_t p = __hip_atomic_load((RK_GLOBAL int32_t *)(lab + (a - 1)), __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t p = l[a - 1];
         if (p == a) return a;
-        const int32_t gp = __hip_atomic_load((RK_GLOBAL int32_t *)(lab + (p - 1)), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t gp = l[p - 1];
         if (gp == p) return p;
         __hip_atomic_fetch_min((RK_GLOBAL int32_t *)(lab + (a - 1)), gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         a = gp;
+    }
+}
+
+// The same without the halving, once no tree changes any more but by entries
+// moving up to their root.
+__device__ __forceinline__ int32_t g_root(const int32_t *lab, int32_t a) {
+    while (true) {
+        const int32_t p = ((const RK_GLOBAL int32_t *)lab)[a - 1];
+        if (p == a) return a;
+        a = p;
     }
 }
 
@@ -147,8 +159,8 @@ __device__ __forceinline__ void g_union(int32_t *lab, int32_t a, int32_t b) {
         }
         const int32_t old = __hip_atomic_fetch_min((RK_GLOBAL int32_t *)(lab + (a - 1)), b, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
-        if (old == a) return;
-        a = old;
+        if (old == a) return;   // a was a root
+        a = old;                // (smaller than a: the walk ends)
     }
 }
 
@@ -379,9 +391,12 @@ __global__ __launch_bounds__(64) void label_flatten(LabelArgs a) {
         int32_t v[4];
         lab_load4(row, xl, a.w, a.lab_vec, v);
         bool any = false;
+        int32_t last_v = 0, last_r = 0;   // (a lane's pixels mostly share a tile root)
         for (int k = 0; k < 4; ++k) {
             if (v[k] == 0) continue;
-            const int32_t root = g_find(a.lab, v[k]);
+            const int32_t root = v[k] == last_v ? last_r : g_root(a.lab, v[k]);
+            last_v = v[k];
+            last_r = root;
             any |= root != v[k];
             v[k] = root;
             const int32_t self = (int32_t)((int64_t)y * a.pitch_lab + xl + k + 1);
