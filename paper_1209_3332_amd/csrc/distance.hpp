@@ -17,7 +17,9 @@
 //             column of one segment: it holds the segment's pixels in
 //             registers, takes the nearest 0 above and below the segment from
 //             the other segments' summaries (the nearest segment that has
-//             one), scans down and up and writes g once.
+//             one), scans down and up and writes g once, as 16-bit values
+//             packed into the first half of the row's 32-bit elements (distances
+//             stay below 16384; half the bytes to write and to read back).
 //   edt_rows  one workgroup per row: the row of g is staged in LDS, then
 //             every pixel takes min over x' of (x - x')^2 + g(x')^2,
 //             searched outward from x and stopped once (x - x')^2 alone
@@ -34,14 +36,16 @@ namespace rk {
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int32_t EDT_NONE = 0x3fffffff;   // no 0 pixel in the column
+constexpr uint32_t EDT_NONE16 = 0xffffu;    // the same in 16 bits (a column distance is below the height, at most 16384)
+constexpr uint32_t EDT_FAR = 0x7fffffffu;   // no 0 pixel (any squared distance is below 2^30)
 constexpr int EDT_SEG = 16;                // rows per column segment (held in registers)
 constexpr int EDT_MAX_W = 16384;           // widest row staged in LDS
 
 struct EdtArgs {
     const uint8_t *img;    // input (0 = background)
     int64_t pitch_img;     // bytes
-    int32_t *g;            // column distances, then (mode 0) dist2 in place
-    int64_t pitch_g;       // elements
+    int32_t *g;            // rows of 16-bit column distances, then (mode 0) dist2 in place
+    int64_t pitch_g;       // 32-bit elements
     uint8_t *d8;           // mode 1: D8 output (may be the input image)
     int64_t pitch_d8;      // bytes
     int32_t h, w;
@@ -102,16 +106,19 @@ __global__ void edt_zeros(EdtArgs a) {
     }
 }
 
+__device__ __forceinline__ uint32_t edt_half(int32_t g) { return g == EDT_NONE ? EDT_NONE16 : (uint32_t)g; }
+typedef uint32_t u32x2 __attribute__((vector_size(8)));   // one 8-byte access
+
 // Column pass.  Grid-stride over (segment, column) with consecutive threads on
-// consecutive columns (coalesced byte loads and int32 stores); with dword-
+// consecutive columns (coalesced byte loads and 16-bit stores); with dword-
 // aligned image rows a thread takes 4 adjacent columns at once (dword loads,
-// and 16-byte stores where the distance plane allows them).
+// and 8-byte stores where the distance plane allows them).
 __global__ void edt_cols(EdtArgs a) {
     const int n_seg = (a.h + EDT_SEG - 1) / EDT_SEG;
     if (((((uintptr_t)a.img) | (uintptr_t)a.pitch_img | (uintptr_t)a.w) & 3u) == 0) {
         const int w4 = a.w / 4;
         const int64_t n4 = (int64_t)n_seg * w4;
-        const bool vec = ((((uintptr_t)a.g) | (uintptr_t)(a.pitch_g * 4)) & 15u) == 0;
+        const bool vec = ((((uintptr_t)a.g) | (uintptr_t)(a.pitch_g * 4)) & 7u) == 0;
         for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n4; q += (int64_t)gridDim.x * blockDim.x) {
             const int x = (int)(q % w4) * 4;
             const int s = (int)(q / w4);
@@ -159,17 +166,13 @@ __global__ void edt_cols(EdtArgs a) {
 #pragma unroll
             for (int r = 0; r < EDT_SEG; ++r) {
                 if (y0 + r >= a.h) continue;
-                int32_t *row = a.g + (int64_t)(y0 + r) * a.pitch_g + x;
+                uint16_t *row = (uint16_t *)(a.g + (int64_t)(y0 + r) * a.pitch_g) + x;
                 if (vec) {
-                    i32x4 o;
-                    o.x = g[r][0];
-                    o.y = g[r][1];
-                    o.z = g[r][2];
-                    o.w = g[r][3];
-                    *(RK_GLOBAL i32x4 *)row = o;
+                    *(RK_GLOBAL u32x2 *)row = u32x2{edt_half(g[r][0]) | edt_half(g[r][1]) << 16,
+                                                    edt_half(g[r][2]) | edt_half(g[r][3]) << 16};
                 } else {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) ((RK_GLOBAL int32_t *)row)[c] = g[r][c];
+                    for (int c = 0; c < 4; ++c) ((RK_GLOBAL uint16_t *)row)[c] = (uint16_t)edt_half(g[r][c]);
                 }
             }
         }
@@ -217,19 +220,19 @@ __global__ void edt_cols(EdtArgs a) {
             else if (r < last && d != EDT_NONE) d += 1;
             if (d < g[r]) g[r] = d;
         }
-        RK_GLOBAL int32_t *gc = (RK_GLOBAL int32_t *)a.g + x;
+        RK_GLOBAL uint16_t *gc = (RK_GLOBAL uint16_t *)a.g + x;
 #pragma unroll
         for (int r = 0; r < EDT_SEG; ++r)
-            if (y0 + r < a.h) gc[(int64_t)(y0 + r) * a.pitch_g] = g[r];
+            if (y0 + r < a.h) gc[(int64_t)(y0 + r) * a.pitch_g * 2] = (uint16_t)edt_half(g[r]);
     }
 }
 
-__device__ __forceinline__ uint32_t isqrt_cap255(int64_t v) {
-    if (v >= 255 * 255) return 255u;
-    int64_t r = (int64_t)sqrt((double)v);
+__device__ __forceinline__ uint32_t isqrt_cap255(uint32_t v) {
+    if (v >= 255u * 255u) return 255u;
+    uint32_t r = (uint32_t)sqrtf((float)v);   // v < 2^16 is exact in 24 bits; off by one at most
     while (r * r > v) --r;
-    while ((r + 1) * (r + 1) <= v) ++r;
-    return (uint32_t)r;
+    while ((r + 1u) * (r + 1u) <= v) ++r;
+    return r;
 }
 
 // Row pass.  One workgroup (any size) per row, grid-stride over rows; dynamic
@@ -256,58 +259,46 @@ constexpr int EDT_ANCHOR = 256;
 constexpr int EDT_TRY = 64;          // outward steps tried before a pixel is left over
 constexpr int EDT_MAX_PER_THREAD = 64;   // pixels per thread and row (16384 / 256); a mask bit each
 
-// In LDS a column distance takes 16 bits (it is below the height, at most
-// 16384); EDT_NONE16 marks a column without a 0 pixel.
-constexpr uint32_t EDT_NONE16 = 0xffffu;
-
-__device__ __forceinline__ int64_t edt_f(RK_LDS const uint16_t *row, int x, int i) {
+// Squared distances stay below 2^30 (both coordinates below 16384), so 32 bits
+// hold them; EDT_FAR is above all of them.
+__device__ __forceinline__ uint32_t edt_f(RK_LDS const uint16_t *row, int x, int i) {
     const uint32_t v = row[i];
-    return v == EDT_NONE16 ? INT64_MAX : (int64_t)(x - i) * (x - i) + (int64_t)v * v;
+    return v == EDT_NONE16 ? EDT_FAR : (uint32_t)((x - i) * (x - i)) + v * v;
 }
 
 // Minimum of f_i(x) over i in [lo, hi], visiting columns by increasing |x - i|
-// and stopping once (x - i)^2 reaches the best value found, or after
-// max_steps distances; *arg receives a minimising column (-1 if every visited
-// column is EDT_NONE) and *done whether the search ended by itself (the
-// minimum is exact) rather than at max_steps.
-__device__ __forceinline__ int64_t edt_search(RK_LDS const uint16_t *row, int x, int lo, int hi, int max_steps,
-                                              int *arg, bool *done) {
-    int64_t best = INT64_MAX;
+// and stopping once (x - i)^2 reaches the best value found; *arg receives a
+// minimising column (-1 if every visited column is EDT_NONE).
+__device__ __forceinline__ uint32_t edt_search(RK_LDS const uint16_t *row, int x, int lo, int hi, int *arg) {
+    uint32_t best = EDT_FAR;
     int at = -1;
     auto take = [&](int i) {
-        const int64_t f = edt_f(row, x, i);
+        const uint32_t f = edt_f(row, x, i);
         if (f < best) {
             best = f;
             at = i;
         }
     };
-    bool finished = true;
     if (x < lo) {
-        for (int i = lo; i <= hi && (int64_t)(i - x) * (i - x) < best; ++i) take(i);
+        for (int i = lo; i <= hi && (uint32_t)((i - x) * (i - x)) < best; ++i) take(i);
     } else if (x > hi) {
-        for (int i = hi; i >= lo && (int64_t)(x - i) * (x - i) < best; --i) take(i);
+        for (int i = hi; i >= lo && (uint32_t)((x - i) * (x - i)) < best; --i) take(i);
     } else {
         take(x);
-        int step = 1;
-        for (; (x - step >= lo || x + step <= hi) && (int64_t)step * step < best; ++step) {
-            if (step > max_steps) {
-                finished = false;
-                break;
-            }
+        for (int step = 1; (x - step >= lo || x + step <= hi) && (uint32_t)(step * step) < best; ++step) {
             if (x - step >= lo) take(x - step);
             if (x + step <= hi) take(x + step);
         }
     }
     *arg = at;
-    *done = finished;
     return best;
 }
 
-__device__ __forceinline__ void edt_put(const EdtArgs &a, RK_GLOBAL int32_t *gr, int y, int x, int64_t best) {
+__device__ __forceinline__ void edt_put(const EdtArgs &a, RK_GLOBAL int32_t *gr, int y, int x, uint32_t best) {
     if (a.mode == 0)
-        gr[x] = best == INT64_MAX ? 0x7fffffff : (int32_t)best;
+        gr[x] = (int32_t)best;
     else
-        gp(a.d8)[(int64_t)y * a.pitch_d8 + x] = (uint8_t)(best == INT64_MAX ? 255u : isqrt_cap255(best));
+        gp(a.d8)[(int64_t)y * a.pitch_d8 + x] = (uint8_t)(best == EDT_FAR ? 255u : isqrt_cap255(best));
 }
 
 __global__ void edt_rows(EdtArgs a) {
@@ -337,9 +328,12 @@ __global__ void edt_rows(EdtArgs a) {
     int it = 0;
     for (int y = blockIdx.x; y < a.h; y += gridDim.x, ++it) {
         RK_GLOBAL int32_t *gr = (RK_GLOBAL int32_t *)a.g + (int64_t)y * a.pitch_g;
-        for (int x = threadIdx.x; x < w; x += blockDim.x) {
-            const int32_t v = gr[x];
-            row[x] = (uint16_t)(v == EDT_NONE ? EDT_NONE16 : (uint32_t)v);
+        {   // the row's 16-bit values, two at a time
+            const RK_GLOBAL uint32_t *src = (const RK_GLOBAL uint32_t *)gr;
+            for (int x = 2 * threadIdx.x; x < w; x += 2 * blockDim.x) {
+                if (x + 1 < w) *(RK_LDS uint32_t *)(row + x) = src[x >> 1];
+                else row[x] = ((const RK_GLOBAL uint16_t *)gr)[x];
+            }
         }
         __syncthreads();
         if (may_leave && threadIdx.x == 0) left_over[(it + 1) & 1] = 0;
@@ -348,21 +342,15 @@ __global__ void edt_rows(EdtArgs a) {
         int m = 0;
         for (int x = threadIdx.x; x < w; x += blockDim.x, ++m) {
             const uint32_t gx = row[x];
-            int64_t best = gx == EDT_NONE16 ? INT64_MAX : (int64_t)gx * gx;
+            uint32_t best = gx == EDT_NONE16 ? EDT_FAR : gx * gx;
             int step = 1;
-            for (; step < w && (int64_t)step * step < best && step <= EDT_TRY; ++step) {
-                if (x - step >= 0) {
-                    const uint32_t v = row[x - step];
-                    if (v != EDT_NONE16 && (int64_t)step * step + (int64_t)v * v < best)
-                        best = (int64_t)step * step + (int64_t)v * v;
-                }
-                if (x + step < w) {
-                    const uint32_t v = row[x + step];
-                    if (v != EDT_NONE16 && (int64_t)step * step + (int64_t)v * v < best)
-                        best = (int64_t)step * step + (int64_t)v * v;
-                }
+            for (; step < w && (uint32_t)(step * step) < best && step <= EDT_TRY; ++step) {
+                const uint32_t d2 = (uint32_t)(step * step);
+                // (a column of EDT_NONE16 is no nearer than 65535: never the minimum)
+                if (x - step >= 0) best = min(best, d2 + (uint32_t)row[x - step] * row[x - step]);
+                if (x + step < w) best = min(best, d2 + (uint32_t)row[x + step] * row[x + step]);
             }
-            if (step >= w || (int64_t)step * step >= best) edt_put(a, gr, y, x, best);
+            if (step >= w || (uint32_t)(step * step) >= best) edt_put(a, gr, y, x, best);
             else open |= 1ull << m;
         }
         if (open) left_over[it & 1] = 1;   // (only rows wider than EDT_TRY can leave a pixel over)
@@ -374,9 +362,8 @@ __global__ void edt_rows(EdtArgs a) {
             // 1. the anchors' columns, kept in the g row
             for (int k = threadIdx.x; k < n_anchor; k += blockDim.x) {
                 int arg;
-                bool done;
                 const int ax = anchor_x(k);
-                (void)edt_search(row, ax, 0, last, w, &arg, &done);
+                (void)edt_search(row, ax, 0, last, &arg);
                 gr[ax] = arg;
             }
             __syncthreads();
@@ -388,8 +375,7 @@ __global__ void edt_rows(EdtArgs a) {
                 const int lo = gr[k * EDT_ANCHOR];
                 const int hi = gr[anchor_x(k + 1)];
                 int arg;
-                bool done;
-                const int64_t best = lo < 0 ? INT64_MAX : edt_search(row, x, lo, hi, w, &arg, &done);
+                const uint32_t best = lo < 0 ? EDT_FAR : edt_search(row, x, lo, hi, &arg);
                 edt_put(a, gr, y, x, best);
             }
             __syncthreads();
@@ -397,7 +383,7 @@ __global__ void edt_rows(EdtArgs a) {
             for (int k = threadIdx.x; k < n_anchor; k += blockDim.x) {
                 const int ax = anchor_x(k);
                 const int col = gr[ax];
-                edt_put(a, gr, y, ax, col < 0 ? INT64_MAX : edt_f(row, ax, col));
+                edt_put(a, gr, y, ax, col < 0 ? EDT_FAR : edt_f(row, ax, col));
             }
             __syncthreads();
         }
