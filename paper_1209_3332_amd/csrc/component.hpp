@@ -35,11 +35,11 @@
 //   comp_label_local  tile-local labelling of {I != 0} (label.hpp's label_tile)
 //                     into the task's int32 label plane;
 //   comp_label_merge  unions across tile borders (merge_tile);
-//   comp_flatten_max  every pixel's node id becomes its root's, and each pixel
-//                     offers min(J, I) to its root: an atomic maximum on the
-//                     root's own entry of the label plane, encoded as
-//                     ENC + value (ENC is above every node id, so a root
-//                     entry at or above ENC marks a root that has an offer);
+//   comp_offer        each pixel whose min(J, I) is positive offers it to its
+//                     root: an atomic maximum on the root's own entry of the
+//                     label plane, encoded as ENC + value (ENC is above every
+//                     node id, so a root entry at or above ENC marks a root
+//                     that has an offer);
 //   comp_write        the reconstruction: 0 on mask 0, else the value its
 //                     root's entry holds (0 for a root without any offer),
 //                     written as the task's result (into the caller's marker
@@ -216,123 +216,177 @@ __global__ __launch_bounds__(64) void comp_label_merge(TaskTable tt, KArgs a) {
     }
 }
 
-// The root of node id a: every find ends at a root, an entry equal to its own
-// id or at or above COMP_ENC (which only a root's entry becomes).  Plain loads:
-// while this runs, entries only change to an ancestor (a pixel's own final
-// root) or, at roots, to COMP_ENC + offer, so a stale value still leads to the
-// root.  (No path compression here: a pixel's entry must end as its root.)
-__device__ __forceinline__ int32_t comp_find(const int32_t *lab, int32_t a) {
-    while (true) {
-        const int32_t p = ((const RK_GLOBAL int32_t *)lab)[a - 1];
-        if (p == a || p >= COMP_ENC) return a;
-        a = p;
+// The root of node id a, *entry receiving what the root's own entry held: its id,
+// or COMP_ENC + offer (which only a root's entry becomes).  Plain loads: while
+// the route's last two kernels run, entries only change to an ancestor or, at
+// roots, to COMP_ENC + offer, so a stale value still leads to the root.  A node
+// that is further than one step away is pointed straight at its root, so the
+// other pixels of its tile take one step.
+__device__ __forceinline__ int32_t comp_root(int32_t *lab, int32_t a, int32_t *entry) {
+    const RK_GLOBAL int32_t *l = (const RK_GLOBAL int32_t *)lab;
+    int32_t p = l[a - 1];
+    if (p == a || p >= COMP_ENC) {
+        *entry = p;
+        return a;
     }
+    int32_t r = p;
+    for (p = l[r - 1]; p != r && p < COMP_ENC; p = l[r - 1]) {
+        __hip_atomic_store((RK_GLOBAL int32_t *)(lab + (a - 1)), p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        r = p;
+    }
+    *entry = p;
+    return r;
 }
 
+// Rows of a unit of the last two kernels: their loads go out together.  Both are
+// bound by the latency of the walks from a pixel to its root: one row at a time,
+// with every entry rewritten as its root's, they took 32-40 us and 14 us for the
+// hole filling of a 2048 x 2048 mask, now 11 and 11.
+constexpr int COMP_ROWS = 4;
+
+// The offers.  Only a positive min(J, I) can raise anything, so a pixel without
+// one reads no label: hole filling, whose marker is the image frame, leaves
+// almost all of the label plane alone here.  A lane sums up neighbouring pixels
+// of one component, and the wave the lanes that share the first one's root (one
+// component mostly fills the row), before they reach the root's entry.
 template <int BH>
-__global__ __launch_bounds__(64) void comp_flatten_max(TaskTable tt, KArgs a) {
+__global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
     if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
     const int ln = lane_id();
-    const uint64_t n = (uint64_t)total_blocks_of(tt) * BH;
+    constexpr int PER = BH / COMP_ROWS;
+    const uint64_t n = (uint64_t)total_blocks_of(tt) * PER;
     UnitWalk wk;
     for (uint64_t u = blockIdx.x; u < n; u += gridDim.x) {
-        const uint32_t gb = (uint32_t)(u / BH);
+        const uint32_t gb = (uint32_t)(u / PER);
         wk.at(tt, gb);
         const TaskDev &t = wk.t;
         if (!on_component_route(a, t, wk.cur)) continue;
         const int lb = (int)(gb - t.block0);
-        const int y = (lb / t.nbx) * BH + (int)(u % BH), x0 = (lb % t.nbx) * BW;
-        if (y >= t.h) continue;
+        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * COMP_ROWS, x0 = (lb % t.nbx) * BW;
+        if (y0 >= t.h) continue;
         const int x = x0 + 4 * ln;
         const int valid = min(4, t.w - x);
-        int32_t *row = t.lab + (int64_t)y * t.pitch_lab;
-        int32_t v[4] = {0, 0, 0, 0};
-        if (valid > 0) lab_load4(row, x, t.w, 1, v);   // label rows are 16-byte aligned (pitch a multiple of 4)
-        // the offers: min(J, I) of the foreground pixels, J the task's initial
-        // marker (the caller's for a dilation, else derived here: no marker
-        // plane is prepared for a task on this route)
-        uint32_t jm = 0;
-        if (valid > 0) {
-            const uint8_t *jrow = t.j + (int64_t)y * t.pitch_j;
-            const uint32_t j0 = t.op == OP_DILATE ? gload4(jrow, x, valid, t.aligned) : initial_marker4(t, jrow, y, x, valid);
-            jm = bmin4(j0, mask4(t, y, x, valid));
+        // min(J, I), J the task's initial marker (the caller's for a dilation,
+        // else derived here: no marker plane is prepared for a task on this route)
+        uint32_t jm[COMP_ROWS], some = 0;
+#pragma unroll
+        for (int r = 0; r < COMP_ROWS; ++r) {
+            const int y = y0 + r;
+            jm[r] = 0;
+            if (y < t.h && valid > 0) {
+                const uint8_t *jrow = t.j + (int64_t)y * t.pitch_j;
+                const uint32_t j0 = t.op == OP_DILATE ? gload4(jrow, x, valid, t.aligned) : initial_marker4(t, jrow, y, x, valid);
+                if (j0 != 0u) jm[r] = bmin4(j0, mask4(t, y, x, valid));
+            }
+            some |= jm[r];
         }
         int32_t root = 0;       // the lane's current root and the largest offer made to it
         uint32_t best = 0;
-        int32_t last_v = 0, last_r = 0;   // the lane's pixels mostly share one tile root: one find for them
-        for (int k = 0; k < 4 && k < valid; ++k) {
-            if (v[k] == 0) continue;   // mask 0
-            const int32_t self = (int32_t)((int64_t)y * t.pitch_lab + x + k + 1);
-            // v[k] at or above COMP_ENC: this pixel is a root that already has an offer
-            int32_t r;
-            if (v[k] >= COMP_ENC) {
-                r = self;
-            } else if (v[k] == last_v) {
-                r = last_r;
-            } else {
-                r = comp_find(t.lab, v[k]);
-                last_v = v[k];
-                last_r = r;
-            }
-            if (r != v[k] && v[k] < COMP_ENC)   // a non-root points straight at its root
-                __hip_atomic_store((RK_GLOBAL int32_t *)(row + x + k), r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t off = byte_of(jm, k);
-            if (r != root) {
-                if (root != 0 && best != 0)
-                    __hip_atomic_fetch_max((RK_GLOBAL int32_t *)(t.lab + (root - 1)), COMP_ENC + (int32_t)best,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                root = r;
-                best = 0;
-            }
-            best = max(best, off);
-        }
-        // a zero offer never raises anything: only positive ones reach the root,
-        // and only when above what its entry shows already
-        if (root != 0 && best != 0) {
-            int32_t *slot = t.lab + (root - 1);
+        auto offer = [&](int32_t r, uint32_t v) {   // (only when above what the entry shows already)
+            int32_t *slot = t.lab + (r - 1);
             const int32_t seen = __hip_atomic_load((RK_GLOBAL int32_t *)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (seen < COMP_ENC + (int32_t)best)
-                __hip_atomic_fetch_max((RK_GLOBAL int32_t *)slot, COMP_ENC + (int32_t)best, __ATOMIC_RELAXED,
+            if (seen < COMP_ENC + (int32_t)v)
+                __hip_atomic_fetch_max((RK_GLOBAL int32_t *)slot, COMP_ENC + (int32_t)v, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
+        };
+        if (some != 0u) {
+            int32_t v[COMP_ROWS][4];
+#pragma unroll
+            for (int r = 0; r < COMP_ROWS; ++r) {
+                v[r][0] = v[r][1] = v[r][2] = v[r][3] = 0;
+                if (jm[r] != 0u) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, 1, v[r]);
+            }
+            int32_t last_v = 0, last_r = 0;   // the lane's pixels mostly share one tile root: one find for them
+#pragma unroll
+            for (int r = 0; r < COMP_ROWS; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t off = byte_of(jm[r], k);
+                    if (off == 0u) continue;
+                    int32_t e = v[r][k];
+                    if (e >= COMP_ENC) {          // this pixel is a root that already has an offer
+                        e = (int32_t)((int64_t)(y0 + r) * t.pitch_lab + x + k + 1);
+                    } else {
+                        if (e != last_v) {
+                            int32_t entry;
+                            last_v = e;
+                            last_r = comp_root(t.lab, e, &entry);
+                        }
+                        e = last_r;
+                    }
+                    if (e != root) {
+                        if (best != 0u) offer(root, best);
+                        root = e;
+                        best = 0;
+                    }
+                    best = max(best, off);
+                }
         }
+        const uint64_t lanes = __ballot(best != 0u);
+        if (lanes == 0ull) continue;
+        const int first = __builtin_ctzll(lanes);
+        const int32_t shared = __builtin_amdgcn_readlane(root, first);
+        const bool with = best != 0u && root == shared;
+        const uint32_t top = (uint32_t)__builtin_amdgcn_readlane((int)wave_prefix_max(with ? best : 0u), LANES - 1);
+        if (ln == first) offer(shared, top);
+        else if (best != 0u && !with) offer(root, best);
     }
 }
 
+// The result: every pixel's root is looked up here (a pixel points at its tile's
+// root, and that one, from the merge or from an earlier look-up, at or near the
+// component's).
 template <int BH>
 __global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
     if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
     const int ln = lane_id();
-    const uint64_t n = (uint64_t)total_blocks_of(tt) * BH;
+    constexpr int PER = BH / COMP_ROWS;
+    const uint64_t n = (uint64_t)total_blocks_of(tt) * PER;
     UnitWalk wk;
     for (uint64_t u = blockIdx.x; u < n; u += gridDim.x) {
-        const uint32_t gb = (uint32_t)(u / BH);
+        const uint32_t gb = (uint32_t)(u / PER);
         wk.at(tt, gb);
         const TaskDev &t = wk.t;
         if (!on_component_route(a, t, wk.cur)) continue;
         const int lb = (int)(gb - t.block0);
-        const int y = (lb / t.nbx) * BH + (int)(u % BH), x0 = (lb % t.nbx) * BW;
-        if (y >= t.h) continue;
-        if (lb == 0 && u % BH == 0 && ln == 0)   // one count per task that took the route
+        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * COMP_ROWS, x0 = (lb % t.nbx) * BW;
+        if (y0 >= t.h) continue;
+        if (lb == 0 && u % PER == 0 && ln == 0)   // one count per task that took the route
             __hip_atomic_fetch_add(&a.work->stat_route, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int x = x0 + 4 * ln;
         const int valid = min(4, t.w - x);
         if (valid <= 0) continue;
-        const int32_t *row = t.lab + (int64_t)y * t.pitch_lab;
-        int32_t ev[4];
-        lab_load4(row, x, t.w, 1, ev);
-        uint32_t out = 0;
-        for (int k = 0; k < 4 && k < valid; ++k) {
-            const int32_t e = ev[k];
-            if (e == 0) continue;                   // mask 0
-            const int32_t r = e >= COMP_ENC ? e : t.lab[e - 1];   // own entry (a root) or the root's
-            if (r >= COMP_ENC) out |= (uint32_t)(r - COMP_ENC) << (8 * k);
+        int32_t e[COMP_ROWS][4];
+#pragma unroll
+        for (int r = 0; r < COMP_ROWS; ++r) {
+            e[r][0] = e[r][1] = e[r][2] = e[r][3] = 0;
+            if (y0 + r < t.h) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, 1, e[r]);
         }
-        // the result itself: the reconstruction into the caller's marker for a
-        // dilation, else mapped into the task's result plane
-        if (t.op == OP_DILATE)
-            gstore4(t.j + (int64_t)y * t.pitch_j, x, valid, t.aligned, out);
-        else
-            gstore4(t.img + (int64_t)y * t.pitch_img, x, valid, t.aligned, mapped_result4(t, out, y, x, valid));
+        int32_t last_e = 0;
+        uint32_t last_val = 0;
+#pragma unroll
+        for (int r = 0; r < COMP_ROWS; ++r) {
+            const int y = y0 + r;
+            if (y >= t.h) break;
+            uint32_t out = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                int32_t ent = e[r][k];
+                if (ent == 0) continue;                   // mask 0
+                if (ent != last_e) {
+                    last_e = ent;
+                    if (ent < COMP_ENC) (void)comp_root(t.lab, ent, &ent);
+                    last_val = ent >= COMP_ENC ? (uint32_t)(ent - COMP_ENC) : 0u;
+                }
+                out |= last_val << (8 * k);
+            }
+            // the result itself: the reconstruction into the caller's marker for a
+            // dilation, else mapped into the task's result plane
+            if (t.op == OP_DILATE)
+                gstore4(t.j + (int64_t)y * t.pitch_j, x, valid, t.aligned, out);
+            else
+                gstore4(t.img + (int64_t)y * t.pitch_img, x, valid, t.aligned, mapped_result4(t, out, y, x, valid));
+        }
     }
 }
 

@@ -492,7 +492,7 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         // reset_work took already decided every route), then label and
         // reconstruct the two-valued ones (the others' waves exit at once)
         const int bh = kUnitRows[v];
-        const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * bh, 4096));
+        const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::COMP_ROWS), 4096));
         const int g_tiles = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::LT_H), 4096));
         const size_t lds_lab = (size_t)rk::LT_H * rk::LT_W * sizeof(uint32_t);
 #define RK_COMP(K, GRID, LDS)                                                                     \
@@ -522,7 +522,7 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         }
         RK_COMP(comp_label_local, g_tiles, lds_lab);
         RK_COMP(comp_label_merge, g_tiles, 0);
-        RK_COMP(comp_flatten_max, g_rows, 0);
+        RK_COMP(comp_offer, g_rows, 0);
         RK_COMP(comp_write, g_rows, 0);
 #undef RK_COMP
         if (timing) HIP_TRY(hipEventRecord(tev[6], s));

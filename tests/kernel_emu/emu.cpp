@@ -612,7 +612,7 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
                     if (which == 0) { KEMU_PICK(comp_classify) }
                     else if (which == 1) { KEMU_PICK(comp_label_local) }
                     else if (which == 2) { KEMU_PICK(comp_label_merge) }
-                    else if (which == 3) { KEMU_PICK(comp_flatten_max) }
+                    else if (which == 3) { KEMU_PICK(comp_offer) }
                     else { KEMU_PICK(comp_write) }
 #undef KEMU_PICK
                     if (!kemu::run_wave(body, lds_sz)) bad++;
