@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
 }
 
 template <int BH>
-__global__ __launch_bounds__(64) void comp_label_local(TaskTable tt, KArgs a) {
+__global__ __launch_bounds__(64 * LT_WAVES) void comp_label_local(TaskTable tt, KArgs a) {
     if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
     RK_LDS uint32_t *par = (RK_LDS uint32_t *)dyn_lds();
     constexpr int PER = BH / LT_H;

@@ -10,7 +10,7 @@
 // whose pixel count lies in [min_area, max_area] and clears the rest.
 //
 // Method (union-find on the label plane itself, then a rank relabelling):
-//   label_local     one wave per 16 x 256 tile: each row's runs of
+//   label_local     one workgroup per 16 x 256 tile, 4 rows a wave: each row's runs of
 //                   foreground pixels become depth-one trees, then one
 //                   union-find link (LDS atomic min: the larger root under
 //                   the smaller) per pair of touching runs of adjacent rows,
@@ -35,6 +35,8 @@
 namespace rk {
 
 constexpr int LT_H = 16;     // rows of a labelling tile
+constexpr int LT_ROWS = 4;   // rows of a wave of the tile's workgroup
+constexpr int LT_WAVES = LT_H / LT_ROWS;
 constexpr int LT_W = 256;    // columns (64 lanes x 4 pixels)
 constexpr uint32_t LT_BG = 0xffffffffu;
 constexpr int RANK_SEG = 1024;   // bitmap words per scan segment (64 lanes x 16)
@@ -193,9 +195,9 @@ __device__ __forceinline__ uint32_t fg_load4(const LabelArgs &a, int y, int x, i
     return v;
 }
 
-// Phase 1: tile-local labelling.  Grid: one 64-lane workgroup per tile
-// (grid-stride); dynamic LDS: LT_H * LT_W * 4 bytes.  Lane l holds columns
-// 4l..4l+3 of every row.
+// Phase 1: tile-local labelling.  Grid: one workgroup of LT_WAVES waves per tile
+// (grid-stride); dynamic LDS: LT_H * LT_W * 4 bytes.  Wave v holds rows
+// LT_ROWS * v.. of the tile, lane l columns 4l..4l+3 of each.
 //   a. runs: every foreground pixel's parent is the first pixel of its run of
 //      foreground pixels in the row (one prefix maximum over the lanes of the
 //      last background column), so a run is a tree of depth one;
@@ -204,97 +206,103 @@ __device__ __forceinline__ uint32_t fg_load4(const LabelArgs &a, int y, int x, i
 //      diagonally under (8-conn) the upper run's first pixel inside the
 //      window the run can reach;
 //   c. path compression; d. node ids out.
-// label_tile is one tile (all lanes of the wave; `par` holds LT_H * LT_W
+// label_tile is one tile (all waves of the workgroup; `par` holds LT_H * LT_W
 // words of LDS); label_local runs it over the tiles of one image.
-// Bound by LDS latency at the 10 waves a compute unit's LDS holds, so the links
-// and the compression go through each lane's own list of bits (a step of the
-// wave serves every lane that has something left) and the ids of all rows are
-// looked up side by side: 43 us on the 4096 x 4096 binary tile (16 MB read, 64
-// MB written: 1.9 TB/s), against 65 with a wave step per pixel position and row.
+// Bound by chains of LDS accesses, so a tile's rows are spread over LT_WAVES
+// waves (a tile of one wave ran 4 times as long a chain, at the 10 waves a
+// compute unit's LDS then holds), and the links and the compression go through
+// each lane's own list of bits (a step of the wave serves every lane that has
+// something left).  The 4096 x 4096 binary tile takes 23 us (16 MB read, 64 MB
+// written: 3.5 TB/s; 42 with a tile to a wave), a 2048 x 2048 mask, whose 1024
+// tiles leave most of the chip idle, 17 (29).  2 rows a wave: the same.
 __device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int x0, int aligned) {
     const int ln = lane_id();
+    const int r0 = uniform((int)(threadIdx.x >> 6)) * LT_ROWS;   // the wave's first row of the tile
     const int c = 4 * ln;
-    {
-        const int th = min(LT_H, a.h - y0), tw = min(LT_W, a.w - x0);
-        const int valid = min(4, tw - c);
-        uint64_t fg = 0;   // bit 4r+k: pixel (r, c+k) is foreground
-        uint32_t rows[LT_H];   // all loads in flight together
+    const int th = min(LT_H, a.h - y0), tw = min(LT_W, a.w - x0);
+    const int valid = min(4, tw - c);
+    uint32_t fg = 0;   // bit 4(r+1)+k: pixel (r0+r, c+k) is foreground; bits 0..3: the row above the wave's rows
+    uint32_t rows[LT_ROWS];   // all loads in flight together
 #pragma unroll
-        for (int r = 0; r < LT_H; ++r)
-            rows[r] = r < th ? fg_load4(a, y0 + r, x0 + c, valid, aligned) : 0u;
+    for (int r = 0; r < LT_ROWS; ++r)
+        rows[r] = r0 + r < th ? fg_load4(a, y0 + r0 + r, x0 + c, valid, aligned) : 0u;
 #pragma unroll
-        for (int r = 0; r < LT_H; ++r) {
-            const uint32_t v = rows[r];
-            int lb = -1;          // last background column so far in this lane
-            int lbk[4];
+    for (int r = 0; r < LT_ROWS; ++r) {
+        const uint32_t v = rows[r];
+        int lb = -1;          // last background column so far in this lane
+        int lbk[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool f = ((v >> (8 * k)) & 0xffu) != 0u;
-                fg |= (uint64_t)(f ? 1u : 0u) << (4 * r + k);
-                if (!f) lb = c + k;
-                lbk[k] = lb;
-            }
-            // last background column before this lane (-1: none), through
-            // values shifted by one so that 0 is the identity
-            const int excl = (int)from_lower(wave_prefix_max((uint32_t)(lb + 1))) - 1;
-            u32x4 start;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool f = (fg >> (4 * r + k)) & 1u;
-                start[k] = f ? (uint32_t)(r * LT_W + max(excl, lbk[k]) + 1) : LT_BG;
-            }
-            *(RK_LDS u32x4 *)(par + r * LT_W + c) = start;
+        for (int k = 0; k < 4; ++k) {
+            const bool f = ((v >> (8 * k)) & 0xffu) != 0u;
+            fg |= (f ? 1u : 0u) << (4 * r + 4 + k);
+            if (!f) lb = c + k;
+            lbk[k] = lb;
         }
-        __syncthreads();
-        // every pixel's neighbours as bits at its own position (no neighbour
-        // inside the tile: background; the tile borders are joined by label_merge)
-        const uint64_t fl = ((uint64_t)from_lower((uint32_t)(fg >> 32)) << 32) | from_lower((uint32_t)fg);
-        const uint64_t fr = ((uint64_t)from_upper((uint32_t)(fg >> 32)) << 32) | from_upper((uint32_t)fg);
-        const uint64_t left = ((fg & 0x7777777777777777ull) << 1) | ((fl >> 3) & 0x1111111111111111ull);
-        const uint64_t right = ((fg >> 1) & 0x7777777777777777ull) | ((fr & 0x1111111111111111ull) << 3);
-        const uint64_t up = fg << 4, up_left = left << 4, up_right = right << 4;
-        // links, each once per pair of runs (see above); a lane walks through its
-        // own, so that the wave takes as many steps as its busiest lane has links
-        // instead of one per pixel position
-        uint64_t links = a.conn == 8 ? fg & ~left & (up_left | up) : fg & up & ~(left & up_left);
-        for (; links; links &= links - 1) {
-            const int q = __builtin_ctzll(links);
-            const uint32_t i = (uint32_t)((q >> 2) * LT_W + c + (q & 3));
-            lds_union(par, i, i - LT_W - (a.conn == 8 ? (uint32_t)(up_left >> q) & 1u : 0u));
-        }
-        if (a.conn == 8)
-            for (links = fg & ~up & up_right; links; links &= links - 1) {
-                const int q = __builtin_ctzll(links);
-                const uint32_t i = (uint32_t)((q >> 2) * LT_W + c + (q & 3));
-                lds_union(par, i, i - LT_W + 1u);
-            }
-        __syncthreads();
-        // path compression of the run starts (every other pixel's parent is its
-        // run's start, so afterwards its root is two steps away)
-        for (uint64_t starts = fg & ~left; starts; starts &= starts - 1) {
-            const int q = __builtin_ctzll(starts);
-            const uint32_t i = (uint32_t)((q >> 2) * LT_W + c + (q & 3));
-            par[i] = lds_find(par, i);
-        }
-        __syncthreads();
+        // last background column before this lane (-1: none), through
+        // values shifted by one so that 0 is the identity
+        const int excl = (int)from_lower(wave_prefix_max((uint32_t)(lb + 1))) - 1;
+        u32x4 start;
 #pragma unroll
-        for (int r = 0; r < LT_H; ++r) {
-            const u32x4 start = *(const RK_LDS u32x4 *)(par + r * LT_W + c);
-            int32_t ids[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool f = (fg >> (4 * r + k)) & 1u;
-                const uint32_t root = par[f ? start[k] : 0u];
-                const int ry = (int)(root / LT_W), rx = (int)(root % LT_W);
-                ids[k] = f ? (int32_t)((int64_t)(y0 + ry) * a.pitch_lab + x0 + rx + 1) : 0;
-            }
-            if (r < th) lab_store4(a.lab + (int64_t)(y0 + r) * a.pitch_lab, x0 + c, a.w, a.lab_vec, ids);
+        for (int k = 0; k < 4; ++k) {
+            const bool f = (fg >> (4 * r + 4 + k)) & 1u;
+            start[k] = f ? (uint32_t)((r0 + r) * LT_W + max(excl, lbk[k]) + 1) : LT_BG;
         }
-        __syncthreads();
+        *(RK_LDS u32x4 *)(par + (r0 + r) * LT_W + c) = start;
     }
+    __syncthreads();
+    if (r0 > 0) {   // (links move entries meanwhile, but none to or from LT_BG)
+        const u32x4 above = *(const RK_LDS u32x4 *)(par + (r0 - 1) * LT_W + c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fg |= (above[k] != LT_BG ? 1u : 0u) << k;
+    }
+    // every pixel's neighbours as bits at its own position (no neighbour
+    // inside the tile: background; the tile borders are joined by label_merge)
+    const uint32_t left = ((fg & 0x77777777u) << 1) | ((from_lower(fg) >> 3) & 0x11111111u);
+    const uint32_t right = ((fg >> 1) & 0x77777777u) | ((from_upper(fg) & 0x11111111u) << 3);
+    const uint32_t up = fg << 4, up_left = left << 4, up_right = right << 4;
+    const uint32_t own = fg & ~0xfu;
+    const uint32_t base = (uint32_t)((r0 - 1) * LT_W + c);   // of bit 0
+    // links, each once per pair of runs (see above); a lane walks through its
+    // own, so that the wave takes as many steps as its busiest lane has links
+    // instead of one per pixel position
+    uint32_t links = a.conn == 8 ? own & ~left & (up_left | up) : own & up & ~(left & up_left);
+    for (; links; links &= links - 1) {
+        const int q = __builtin_ctz(links);
+        const uint32_t i = base + (uint32_t)((q >> 2) * LT_W + (q & 3));
+        lds_union(par, i, i - LT_W - (a.conn == 8 ? (up_left >> q) & 1u : 0u));
+    }
+    if (a.conn == 8)
+        for (links = own & ~up & up_right; links; links &= links - 1) {
+            const int q = __builtin_ctz(links);
+            const uint32_t i = base + (uint32_t)((q >> 2) * LT_W + (q & 3));
+            lds_union(par, i, i - LT_W + 1u);
+        }
+    __syncthreads();
+    // path compression of the run starts (every other pixel's parent is its
+    // run's start, so afterwards its root is two steps away)
+    for (uint32_t starts = own & ~left; starts; starts &= starts - 1) {
+        const int q = __builtin_ctz(starts);
+        const uint32_t i = base + (uint32_t)((q >> 2) * LT_W + (q & 3));
+        par[i] = lds_find(par, i);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < LT_ROWS; ++r) {
+        const u32x4 start = *(const RK_LDS u32x4 *)(par + (r0 + r) * LT_W + c);
+        int32_t ids[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool f = (fg >> (4 * r + 4 + k)) & 1u;
+            const uint32_t root = par[f ? start[k] : 0u];
+            const int ry = (int)(root / LT_W), rx = (int)(root % LT_W);
+            ids[k] = f ? (int32_t)((int64_t)(y0 + ry) * a.pitch_lab + x0 + rx + 1) : 0;
+        }
+        if (r0 + r < th) lab_store4(a.lab + (int64_t)(y0 + r0 + r) * a.pitch_lab, x0 + c, a.w, a.lab_vec, ids);
+    }
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(64) void label_local(LabelArgs a) {
+__global__ __launch_bounds__(64 * LT_WAVES) void label_local(LabelArgs a) {
     RK_LDS uint32_t *par = (RK_LDS uint32_t *)dyn_lds();
     const int n_tiles = a.tiles_x * ((a.h + LT_H - 1) / LT_H);
     const int aligned = img_aligned(a);
@@ -322,47 +330,79 @@ __global__ __launch_bounds__(64) void label_local(LabelArgs a) {
 // cross-corner neighbours in other tiles is always linked explicitly.  A
 // component spanning many tiles (a background) costs a few unions per tile
 // instead of one per border pixel.
+// Bound by the walks to the roots (a trip to the L2 for every step): all entries
+// that decide the links are loaded at once, a lane then goes through its own
+// links, and those between the pair of nodes that the first lane joins (along a
+// border mostly two large components) are left to that lane.  9.0 us for the
+// 4096 x 4096 binary tile, 16.5 for the background of a 2048 x 2048 mask (10.5 and
+// 18.3 with the neighbours loaded pixel by pixel).
 __device__ void merge_tile(const LabelArgs &a, int y0, int x0) {
     const int ln = lane_id();
     const int th = min(LT_H, a.h - y0), tw = min(LT_W, a.w - x0);
-    auto fg = [&](int y, int x) -> bool {
-        return y >= 0 && y < a.h && x >= 0 && x < a.w && a.lab[(int64_t)y * a.pitch_lab + x] != 0;
+    auto at = [&](int y, int x) -> int32_t {
+        return y >= 0 && y < a.h && x >= 0 && x < a.w ? ((const RK_GLOBAL int32_t *)a.lab)[(int64_t)y * a.pitch_lab + x] : 0;
     };
-    auto node = [&](int y, int x) -> int32_t { return a.lab[(int64_t)y * a.pitch_lab + x]; };
+    const int x = x0 + 4 * ln;
+    int32_t c[4] = {0, 0, 0, 0}, u[4] = {0, 0, 0, 0};   // the tile's top row, the row above it
+    int32_t ul = 0, ur = 0;                             // u[-1], u[4]
     if (y0 > 0) {
-        for (int k = 0; k < 4; ++k) {
-            const int x = x0 + 4 * ln + k;
-            if (x >= x0 + tw || !fg(y0, x)) continue;
-            const bool in = x - 1 >= x0;   // c[x-1] inside this tile
-            const bool cl = in && fg(y0, x - 1), al = fg(y0 - 1, x - 1), au = fg(y0 - 1, x), ar = fg(y0 - 1, x + 1);
-            const int32_t self = node(y0, x);
-            if (a.conn == 8) {
-                if (!cl) {
-                    if (al) g_union(a.lab, self, node(y0 - 1, x - 1));
-                    else if (au) g_union(a.lab, self, node(y0 - 1, x));
-                }
-                if (!au && ar) g_union(a.lab, self, node(y0 - 1, x + 1));
-            } else if (au && (!cl || !(in && al))) {
-                g_union(a.lab, self, node(y0 - 1, x));
-            }
+        if (x < x0 + tw) {
+            lab_load4(a.lab + (int64_t)y0 * a.pitch_lab, x, a.w, a.lab_vec, c);
+            lab_load4(a.lab + (int64_t)(y0 - 1) * a.pitch_lab, x, a.w, a.lab_vec, u);
         }
+        if (ln == 0) ul = at(y0 - 1, x0 - 1);
+        if (ln == LANES - 1) ur = at(y0 - 1, x0 + LT_W);
     }
-    if (x0 > 0) {
-        for (int r = ln; r < th; r += LANES) {
-            const int y = y0 + r;
-            if (!fg(y, x0)) continue;
-            const bool in = r >= 1;   // the pixel above inside this tile
-            const bool cl = in && fg(y - 1, x0), al = fg(y - 1, x0 - 1), au = fg(y, x0 - 1), ar = fg(y + 1, x0 - 1);
-            const int32_t self = node(y, x0);
-            if (a.conn == 8) {
-                if (!cl) {
-                    if (al) g_union(a.lab, self, node(y - 1, x0 - 1));
-                    else if (au) g_union(a.lab, self, node(y, x0 - 1));
-                }
-                if (!au && ar) g_union(a.lab, self, node(y + 1, x0 - 1));
-            } else if (au && (!cl || !(in && al))) {
-                g_union(a.lab, self, node(y, x0 - 1));
-            }
+    // lane l: rows y0 - 1 + l of the tile's left column and the column left of it
+    int32_t cc = 0, cu = 0;
+    if (x0 > 0 && ln <= th + 1) {
+        cc = ln >= 1 && ln <= th ? at(y0 - 1 + ln, x0) : 0;
+        cu = at(y0 - 1 + ln, x0 - 1);
+    }
+    const int32_t cl0 = (int32_t)from_lower((uint32_t)c[3]);   // c[-1]: 0 for the first lane (outside this tile)
+    const int32_t u_lo = (int32_t)from_lower((uint32_t)u[3]), u_up = (int32_t)from_upper((uint32_t)u[0]);
+    if (ln != 0) ul = u_lo;
+    if (ln != LANES - 1) ur = u_up;
+    const int32_t cc_lo = (int32_t)from_lower((uint32_t)cc), cu_lo = (int32_t)from_lower((uint32_t)cu);
+    const int32_t cu_up = (int32_t)from_upper((uint32_t)cu);
+    // links: bit k, the top row's pixel k with o[k]; bit 4 + k, with the pixel
+    // above right of it; bits 8 and 9, the left column's pixel likewise
+    uint32_t links = 0;
+    int32_t o[5];
+    auto link = [&](int bit, int32_t self, bool in, int32_t before, int32_t al, int32_t au, int32_t ar, int32_t &other) {
+        const bool cl = in && before != 0;   // the pixel before it inside this tile
+        other = au;
+        if (self == 0) return;
+        if (a.conn == 8) {
+            if (al != 0) other = al;
+            if (!cl && (al != 0 || au != 0)) links |= 1u << bit;
+            if (au == 0 && ar != 0) links |= 1u << (bit == 8 ? 9 : bit + 4);
+        } else if (au != 0 && (!cl || !(in && al != 0))) {
+            links |= 1u << bit;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        link(k, c[k], k > 0 || ln > 0, k > 0 ? c[k - 1] : cl0, k > 0 ? u[k - 1] : ul, u[k], k < 3 ? u[k + 1] : ur, o[k]);
+    link(8, cc, ln >= 2, cc_lo, cu_lo, cu, cu_up, o[4]);
+    int32_t done_s = 0, done_o = 0;
+    for (uint64_t live = __ballot(links != 0u); live != 0ull; live = __ballot(links != 0u)) {
+        const uint32_t bit = links & (0u - links);
+        links ^= bit;
+        int32_t self = cc, other = bit == 1u << 9 ? cu_up : o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (bit & (0x11u << k)) self = c[k];
+            if (bit == 1u << k) other = o[k];
+            if (bit == 0x10u << k) other = k < 3 ? u[k + 1] : ur;
+        }
+        const int first = __builtin_ctzll(live);
+        const int32_t fs = __builtin_amdgcn_readlane(self, first), fo = __builtin_amdgcn_readlane(other, first);
+        const bool again = (self == done_s && other == done_o) || (ln != first && self == fs && other == fo);
+        if (bit != 0u && !again) {
+            g_union(a.lab, self, other);
+            done_s = self;
+            done_o = other;
         }
     }
 }

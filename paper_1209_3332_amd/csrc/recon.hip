@@ -495,15 +495,15 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::COMP_ROWS), 4096));
         const int g_tiles = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::LT_H), 4096));
         const size_t lds_lab = (size_t)rk::LT_H * rk::LT_W * sizeof(uint32_t);
-#define RK_COMP(K, GRID, LDS)                                                                     \
+#define RK_COMP(K, GRID, THREADS, LDS)                                                                 \
     switch (v) {                                                                                  \
-        case 0: hipLaunchKernelGGL(rk::K<16>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
-        case 1: hipLaunchKernelGGL(rk::K<32>, dim3(GRID), dim3(64), LDS, s, tt, ka); break;      \
+        case 0: hipLaunchKernelGGL(rk::K<16>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break;      \
+        case 1: hipLaunchKernelGGL(rk::K<32>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break;      \
         case 2:                                                                                   \
-        case kRegionSmallV: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(64), LDS, s, tt, ka); break; \
-        default: hipLaunchKernelGGL(rk::K<kUnitRows[kRegionV]>, dim3(GRID), dim3(64), LDS, s, tt, ka); break; \
+        case kRegionSmallV: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break; \
+        default: hipLaunchKernelGGL(rk::K<kUnitRows[kRegionV]>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break; \
     }
-        RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 0);
+        RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 64, 0);
         // A large batch (a replayed graph) forks: the ring and marker planes
         // (prepare) and the revisit kernel of the tasks that keep the block
         // route go to the second stream, while the route's labelling and
@@ -520,10 +520,10 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
             HIP_TRY(hipStreamWaitEvent(c->aux_stream, c->ev_fork, 0));
             d = c->aux_stream;
         }
-        RK_COMP(comp_label_local, g_tiles, lds_lab);
-        RK_COMP(comp_label_merge, g_tiles, 0);
-        RK_COMP(comp_offer, g_rows, 0);
-        RK_COMP(comp_write, g_rows, 0);
+        RK_COMP(comp_label_local, g_tiles, 64 * rk::LT_WAVES, lds_lab);
+        RK_COMP(comp_label_merge, g_tiles, 64, 0);
+        RK_COMP(comp_offer, g_rows, 64, 0);
+        RK_COMP(comp_write, g_rows, 64, 0);
 #undef RK_COMP
         if (timing) HIP_TRY(hipEventRecord(tev[6], s));
         hipLaunchKernelGGL(rk::prepare, dim3(1024), dim3(256), 0, d, tt, ka, any_mapped ? 1 : 0);
@@ -1307,7 +1307,7 @@ static int enqueue_label(const recon_image &img, int32_t *lab, int64_t pitch_lab
     const int g_clear = (int)std::min<uint32_t>((a.n_words + 255) / 256, 4096u);
     const size_t lds = (size_t)rk::LT_H * rk::LT_W * sizeof(uint32_t);
     if (ranks) hipLaunchKernelGGL(rk::clear_words, dim3(g_clear), dim3(256), 0, s, a.bits, a.n_words);
-    hipLaunchKernelGGL(rk::label_local, dim3(g_tiles), dim3(64), lds, s, a);
+    hipLaunchKernelGGL(rk::label_local, dim3(g_tiles), dim3(64 * rk::LT_WAVES), lds, s, a);
     hipLaunchKernelGGL(rk::label_merge, dim3(g_tiles), dim3(64), 0, s, a);
     hipLaunchKernelGGL(rk::label_flatten, dim3(g_rows), dim3(64), 0, s, a);
     if (!ranks) {

@@ -252,6 +252,29 @@ static bool run_wave(const std::function<void()> &body, size_t lds_size, Workgro
 
 }  // namespace kemu
 
+// A grid of n workgroups of `waves` waves each, a thread per wave; the number of
+// waves that ended wrongly.
+static int workgroups(int n, int waves, size_t lds, const std::function<void()> &body) {
+    std::vector<std::unique_ptr<kemu::Workgroup>> wgs;
+    std::vector<std::thread> th;
+    std::atomic<int> bad{0};
+    for (int g = 0; g < n; ++g) {
+        wgs.emplace_back(new kemu::Workgroup());
+        kemu::Workgroup *wg = wgs.back().get();
+        wg->waves = waves;
+        wg->lds.assign(lds, 0xcd);
+        for (int v = 0; v < waves; ++v)
+            th.emplace_back([&, g, v, wg] {
+                kemu::blockIdx_.x = (uint32_t)g;
+                kemu::gridDim_.x = (uint32_t)n;
+                kemu::blockDim_.x = (uint32_t)(64 * waves);
+                if (!kemu::run_wave(body, lds, wg, v)) bad++;
+            });
+    }
+    for (auto &t : th) t.join();
+    return bad;
+}
+
 // ---------------------------------------------------------------------------
 // labelling driver: the phases of recon_label / recon_area_threshold in
 // order, each as a grid of emulated waves on concurrent threads.
@@ -306,7 +329,7 @@ static int emu_label(const uint8_t *img_in, int h, int w, int conn, int n_waves,
         for (auto &t : th) t.join();
     };
     serial([&] { clear_words(a.bits, a.n_words); }, 2, 64);
-    waves(n_waves, (size_t)LT_H * LT_W * 4, [&] { label_local(a); });
+    bad += workgroups(n_waves, LT_WAVES, (size_t)LT_H * LT_W * 4, [&] { label_local(a); });
     waves(n_waves, 0, [&] { label_merge(a); });
     waves(n_waves, 0, [&] { label_flatten(a); });
     std::vector<int32_t> roots((size_t)((h - 1) * pitch_lab + w));   // the flattened plane (root ids)
@@ -594,14 +617,8 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
         for (auto &t : th) t.join();
     };
     if (component) {   // classification, labelling and the per-component maxima, as the library runs them
-        auto comp_grid = [&](int which, size_t lds_sz) {
-            std::vector<std::thread> th;
-            for (int g = 0; g < n_waves; ++g) {
-                th.emplace_back([&, g, which, lds_sz] {
-                    kemu::blockIdx_.x = (uint32_t)g;
-                    kemu::gridDim_.x = (uint32_t)n_waves;
-                    kemu::blockDim_.x = 64;
-                    std::function<void()> body;
+        auto comp_grid = [&](int which, size_t lds_sz, int wg_waves = 1) {
+            std::function<void()> body;
 #define KEMU_PICK(K)                                            \
     switch (bh) {                                               \
         case 16: body = [&] { K<16>(tt, ka); }; break;          \
@@ -609,20 +626,17 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
         case 128: body = [&] { K<128>(tt, ka); }; break;        \
         default: body = [&] { K<64>(tt, ka); }; break;          \
     }
-                    if (which == 0) { KEMU_PICK(comp_classify) }
-                    else if (which == 1) { KEMU_PICK(comp_label_local) }
-                    else if (which == 2) { KEMU_PICK(comp_label_merge) }
-                    else if (which == 3) { KEMU_PICK(comp_offer) }
-                    else { KEMU_PICK(comp_write) }
+            if (which == 0) { KEMU_PICK(comp_classify) }
+            else if (which == 1) { KEMU_PICK(comp_label_local) }
+            else if (which == 2) { KEMU_PICK(comp_label_merge) }
+            else if (which == 3) { KEMU_PICK(comp_offer) }
+            else { KEMU_PICK(comp_write) }
 #undef KEMU_PICK
-                    if (!kemu::run_wave(body, lds_sz)) bad++;
-                });
-            }
-            for (auto &t : th) t.join();
+            bad += workgroups(n_waves, wg_waves, lds_sz, body);
         };
         comp_grid(0, 0);   // the classification; its last workgroup decides the routes
         grid_run([&] { prepare(tt, ka, any_mapped ? 1 : 0); }, 8, 64);
-        comp_grid(1, (size_t)LT_H * LT_W * 4);
+        comp_grid(1, (size_t)LT_H * LT_W * 4, LT_WAVES);
         comp_grid(2, 0);
         comp_grid(3, 0);
         comp_grid(4, 0);
@@ -633,25 +647,10 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
     if (stop_after >= 2) run_grid(2, n_waves);
     if (region) {   // the region kernel: n_waves workgroups, a thread per wave
         const size_t words = bh == 128 ? region_lds_bytes<16, 8>() : region_lds_bytes<4, 2>();
-        std::vector<std::unique_ptr<kemu::Workgroup>> wgs;
-        std::vector<std::thread> th;
-        for (int g = 0; g < n_waves; ++g) {
-            wgs.emplace_back(new kemu::Workgroup());
-            kemu::Workgroup *wg = wgs.back().get();
-            wg->waves = region_waves;
-            wg->lds.assign(words, 0xcd);
-            for (int v = 0; v < region_waves; ++v)
-                th.emplace_back([&, g, v, wg] {
-                    kemu::blockIdx_.x = (uint32_t)g;
-                    kemu::gridDim_.x = (uint32_t)n_waves;
-                    kemu::blockDim_.x = (uint32_t)(64 * region_waves);
-                    std::function<void()> body;
-                    if (bh == 128) body = [&] { region_drain<16, 8>(tt, ka); };
-                    else body = [&] { region_drain<4, 2>(tt, ka); };
-                    if (!kemu::run_wave(body, words, wg, v)) bad++;
-                });
-        }
-        for (auto &t : th) t.join();
+        std::function<void()> body;
+        if (bh == 128) body = [&] { region_drain<16, 8>(tt, ka); };
+        else body = [&] { region_drain<4, 2>(tt, ka); };
+        bad += workgroups(n_waves, region_waves, words, body);
     } else if (merged || stop_after >= 3) {
         run_grid(3, n_waves);
     }
