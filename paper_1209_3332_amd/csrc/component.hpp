@@ -87,48 +87,58 @@ struct UnitWalk {
     }
 };
 
-// Classification: one wave per block of up to 32 rows, or 32 rows of a higher
-// one (grid-stride), the rows loaded together; each lane keeps the OR and AND of its nonzero mask bytes, the
-// wave combines them once per task it leaves, and only a combination that
-// changes a task's words is written.  A wave skips the blocks of a task whose
-// words already show two different nonzero values (it can never take the
-// route); the words are read with plain loads there, a stale copy only
-// skipping less.
+// Classification: one workgroup of CLASS_WAVES waves per block of up to 32 rows, or
+// 32 rows of a higher one (grid-stride), a wave's rows loaded together; each lane
+// keeps the OR and AND of its nonzero mask bytes, a wave combines them once per
+// task it leaves, and only a combination that changes a task's words is written
+// (the words are read with plain loads first: a stale copy holds no bit that the
+// current one lacks, so what it already shows need not be written).  A wave skips
+// the blocks of a task whose words already show two different nonzero values (it
+// can never take the route).
+// Bound by its chain: table, words, rows, then one count per workgroup on a
+// single word; so a workgroup covers many rows and a wave few: 15 us for one
+// 2048 x 2048 mask, 21 with 32 rows to a wave and a wave to a workgroup.
+constexpr int CLASS_WAVES = 4;
+
 template <int BH>
-__global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
+__global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, KArgs a) {
     if (a.work->classify_skip == seq_of(tt)) return;   // the samples decided every route
-    const int ln = lane_id();
-    constexpr int CH = BH < 32 ? BH : 32;   // rows of a unit, their loads in flight together
-    constexpr int PER = BH / CH;
+    const int ln = lane_id(), wv = uniform((int)(threadIdx.x >> 6));
+    RK_LDS uint32_t *wrote_wv = (RK_LDS uint32_t *)dyn_lds();   // per wave: it changed a route word or has_grey
+    constexpr int UH = BH < 32 ? BH : 32;         // rows of a unit
+    constexpr int CH = UH / CLASS_WAVES;          // rows of a wave, their loads in flight together
+    constexpr int PER = BH / UH;
     const uint32_t n = total_blocks_of(tt) * PER;
     UnitWalk wk;
     int acc_k = -1;                 // task whose partial OR / AND this wave holds
-    uint32_t acc_or = 0, acc_and = 0xffu;
+    uint32_t acc_or = 0, acc_and = 0xffffffffu;   // four bytes side by side
+    uint32_t seen_or = 0, seen_and = 0;           // its words as read last
     const uint32_t seq = seq_of(tt);
-    bool wrote = false;             // (lane 0) this workgroup changed a route word or has_grey
+    bool wrote = false;
     auto flush = [&]() {
         if (acc_k < 0) return;
+        acc_or |= acc_or >> 16;
+        acc_and &= acc_and >> 16;
+        acc_or = (acc_or | acc_or >> 8) & 0xffu;
+        acc_and = (acc_and & acc_and >> 8) & 0xffu;
         for (int d = 1; d < LANES; d <<= 1) {
             acc_or |= (uint32_t)__shfl_xor((int)acc_or, d);
             acc_and &= (uint32_t)__shfl_xor((int)acc_and, d);
         }
-        if (ln == 0) {
+        if (ln == 0 && ((acc_or & ~seen_or) | (seen_and & ~acc_and)) != 0u) {
             uint32_t *wo = a.route + ROUTE_WORDS * acc_k, *wa = wo + 1;
-            const uint32_t co = __hip_atomic_load(wo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((co | acc_or) != co) __hip_atomic_fetch_or(wo, acc_or, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t ca = __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((ca & acc_and) != ca) __hip_atomic_fetch_and(wa, acc_and, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t no = co | acc_or, na = ca & acc_and;
-            wrote |= (no != co) || (na != ca);
+            if ((acc_or & ~seen_or) != 0u) __hip_atomic_fetch_or(wo, acc_or, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((seen_and & ~acc_and) != 0u) __hip_atomic_fetch_and(wa, acc_and, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wrote = true;
+            // (read back after both: of the waves that make a task grey together, the last one sees it)
+            const uint32_t no = __hip_atomic_load(wo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t na = __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // this task is grey (any writer, same value; a plain load first so
             // that a line already holding it is not written again by every wave)
-            if (no != 0u && no != na && a.work->has_grey != seq) {
-                a.work->has_grey = seq;
-                wrote = true;
-            }
+            if (no != 0u && no != na && a.work->has_grey != seq) a.work->has_grey = seq;
         }
         acc_or = 0;
-        acc_and = 0xffu;
+        acc_and = 0xffffffffu;
     };
     for (uint32_t u = blockIdx.x; u < n; u += gridDim.x) {
         const uint32_t gb = u / PER;
@@ -140,7 +150,8 @@ __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
             acc_k = wk.cur;
         }
         const uint32_t *rw = a.route + ROUTE_WORDS * wk.cur;
-        const uint32_t seen_or = rw[0], seen_and = rw[1];
+        seen_or = rw[0];
+        seen_and = rw[1];
         if (uniform(seen_or != 0u && seen_or != seen_and ? 1 : 0)) continue;
         // a thick mask beside grey work keeps the block route whatever its
         // values (decide_tasks), so it is not read either
@@ -149,30 +160,32 @@ __global__ __launch_bounds__(64) void comp_classify(TaskTable tt, KArgs a) {
         const BlockGeom g = geom<BH>(t, lb / t.nbx, lb % t.nbx);
         const int x = g.x0 + 4 * ln;
         const int valid = min(4, g.bw - 4 * ln);
-        const int r0 = (int)(u % PER) * CH;
+        const int r0 = (int)(u % PER) * UH + wv * CH;
         uint32_t m[CH];
 #pragma unroll
         for (int r = 0; r < CH; ++r) m[r] = (r0 + r < g.bh && valid > 0) ? mask4(t, g.y0 + r0 + r, x, valid) : 0u;
 #pragma unroll
-        for (int r = 0; r < CH; ++r)
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t b = byte_of(m[r], j);
-                if (b) {
-                    acc_or |= b;
-                    acc_and &= b;
-                }
-            }
+        for (int r = 0; r < CH; ++r) {
+            const uint32_t zero = ~(m[r] | ((m[r] & 0x7f7f7f7fu) + 0x7f7f7f7fu)) & 0x80808080u;   // of the bytes that are 0
+            acc_or |= m[r];
+            acc_and &= m[r] | (zero >> 7) * 0xffu;
+        }
     }
     flush();
     // the last workgroup to finish decides every task's route (decide_tasks):
     // a workgroup that wrote releases its writes with its count, and the last
     // one acquires them all (an agent-scope release or acquire writes back or
     // invalidates this XCD's L2, so the others neither fence nor acquire)
+    if (ln == 0) wrote_wv[wv] = wrote ? 1u : 0u;
+    __syncthreads();
+    if (wv != 0) return;
     uint32_t prior = 0;
     if (ln == 0) {
+        uint32_t any = 0;
+        for (int v = 0; v < CLASS_WAVES; ++v) any |= wrote_wv[v];
         uint32_t *cnt = &a.work->classify_done;
-        prior = wrote ? __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT)
-                      : __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        prior = any ? __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT)
+                    : __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (uniform(prior) + 1u == gridDim.x) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
