@@ -67,7 +67,6 @@ __device__ __forceinline__ LabelArgs comp_label_args(const TaskDev &t) {
     la.conn = t.conn;
     la.tiles_x = t.nbx;     // LT_W == BW: a block column is a tile column
     la.bits = nullptr;
-    la.lab_vec = 1;   // the planes are 256-byte aligned with a pitch of a multiple of 4 elements
     la.fg_inv = t.minv;
     return la;
 }
@@ -208,7 +207,7 @@ __global__ __launch_bounds__(64 * LT_WAVES) void comp_label_local(TaskTable tt, 
         const int y0 = (lb / wk.t.nbx) * BH + (int)(u % PER) * LT_H, x0 = (lb % wk.t.nbx) * BW;
         if (y0 >= wk.t.h) continue;
         const LabelArgs la = comp_label_args(wk.t);
-        label_tile(la, par, y0, x0, img_aligned(la));
+        label_tile(la, par, y0, x0);
     }
 }
 
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
             jm[r] = 0;
             if (y < t.h && valid > 0) {
                 const uint8_t *jrow = t.j + (int64_t)y * t.pitch_j;
-                const uint32_t j0 = t.op == OP_DILATE ? gload4(jrow, x, valid, t.aligned) : initial_marker4(t, jrow, y, x, valid);
+                const uint32_t j0 = t.op == OP_DILATE ? gload4(jrow, x, valid) : initial_marker4(t, jrow, y, x, valid);
                 if (j0 != 0u) jm[r] = bmin4(j0, mask4(t, y, x, valid));
             }
             some |= jm[r];
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
 #pragma unroll
             for (int r = 0; r < COMP_ROWS; ++r) {
                 v[r][0] = v[r][1] = v[r][2] = v[r][3] = 0;
-                if (jm[r] != 0u) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, 1, v[r]);
+                if (jm[r] != 0u) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, v[r]);
             }
             int32_t last_v = 0, last_r = 0;   // the lane's pixels mostly share one tile root: one find for them
 #pragma unroll
@@ -373,7 +372,7 @@ __global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
 #pragma unroll
         for (int r = 0; r < COMP_ROWS; ++r) {
             e[r][0] = e[r][1] = e[r][2] = e[r][3] = 0;
-            if (y0 + r < t.h) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, 1, e[r]);
+            if (y0 + r < t.h) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, e[r]);
         }
         int32_t last_e = 0;
         uint32_t last_val = 0;
@@ -396,9 +395,9 @@ __global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
             // the result itself: the reconstruction into the caller's marker for a
             // dilation, else mapped into the task's result plane
             if (t.op == OP_DILATE)
-                gstore4(t.j + (int64_t)y * t.pitch_j, x, valid, t.aligned, out);
+                gstore4(t.j + (int64_t)y * t.pitch_j, x, valid, out);
             else
-                gstore4(t.img + (int64_t)y * t.pitch_img, x, valid, t.aligned, mapped_result4(t, out, y, x, valid));
+                gstore4(t.img + (int64_t)y * t.pitch_img, x, valid, mapped_result4(t, out, y, x, valid));
         }
     }
 }

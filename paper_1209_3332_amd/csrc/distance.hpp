@@ -33,8 +33,6 @@
 
 namespace rk {
 
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int32_t EDT_NONE = 0x3fffffff;   // no 0 pixel in the column
 constexpr uint32_t EDT_NONE16 = 0xffffu;    // the same in 16 bits (a column distance is below the height, at most 16384)
 constexpr uint32_t EDT_FAR = 0x7fffffffu;   // no 0 pixel (any squared distance is below 2^30)

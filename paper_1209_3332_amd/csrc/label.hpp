@@ -55,17 +55,16 @@ struct LabelArgs {
     uint32_t n_words;
     uint32_t n_segs;
     int32_t *count;         // receives the number of components (may be null)
-    int32_t lab_vec;        // 1: the label plane allows 16-byte accesses (base and row pitch)
     int32_t fg_inv;         // 1: the foreground is the pixels below 255 (the complement's nonzero pixels)
 };
 
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // (element-aligned: all that an access needs)
 
 // 4 label elements at columns x..x+3 of a row (x a multiple of 4); elements
 // at or past w read 0 and are not written.
-__device__ __forceinline__ void lab_load4(const int32_t *row, int x, int w, int vec, int32_t v[4]) {
-    if (vec && x + 4 <= w) {
-        const i32x4 q = *(const RK_GLOBAL i32x4 *)(row + x);
+__device__ __forceinline__ void lab_load4(const int32_t *row, int x, int w, int32_t v[4]) {
+    if (x + 4 <= w) {
+        const i32x4_any q = *(const RK_GLOBAL i32x4_any *)(row + x);
         v[0] = q.x;
         v[1] = q.y;
         v[2] = q.z;
@@ -75,14 +74,14 @@ __device__ __forceinline__ void lab_load4(const int32_t *row, int x, int w, int 
     for (int k = 0; k < 4; ++k) v[k] = x + k < w ? ((const RK_GLOBAL int32_t *)row)[x + k] : 0;
 }
 
-__device__ __forceinline__ void lab_store4(int32_t *row, int x, int w, int vec, const int32_t v[4]) {
-    if (vec && x + 4 <= w) {
-        i32x4 q;
+__device__ __forceinline__ void lab_store4(int32_t *row, int x, int w, const int32_t v[4]) {
+    if (x + 4 <= w) {
+        i32x4_any q;
         q.x = v[0];
         q.y = v[1];
         q.z = v[2];
         q.w = v[3];
-        *(RK_GLOBAL i32x4 *)(row + x) = q;
+        *(RK_GLOBAL i32x4_any *)(row + x) = q;
         return;
     }
     for (int k = 0; k < 4; ++k)
@@ -166,10 +165,6 @@ __device__ __forceinline__ void g_union(int32_t *lab, int32_t a, int32_t b) {
     }
 }
 
-__device__ __forceinline__ int img_aligned(const LabelArgs &a) {
-    return (((uintptr_t)a.img | (uintptr_t)a.pitch_img) & 3u) == 0;
-}
-
 // inclusive prefix maximum over the 64 lanes of a wave (unsigned values; 0
 // is the identity): DPP row shifts inside each 16-lane row, then the totals of
 // the rows before through readlane
@@ -186,8 +181,8 @@ __device__ __forceinline__ uint32_t wave_prefix_max(uint32_t v) {
 
 // The 4 pixels at columns x..x+3 of row y as foreground bytes: nonzero where
 // the pixel is foreground (fg_inv: below 255), 0 elsewhere and past the image.
-__device__ __forceinline__ uint32_t fg_load4(const LabelArgs &a, int y, int x, int valid, int aligned) {
-    uint32_t v = gload4(a.img + (int64_t)y * a.pitch_img, x, valid, aligned);
+__device__ __forceinline__ uint32_t fg_load4(const LabelArgs &a, int y, int x, int valid) {
+    uint32_t v = gload4(a.img + (int64_t)y * a.pitch_img, x, valid);
     if (a.fg_inv) {
         const uint32_t keep = valid >= 4 ? 0xffffffffu : (valid <= 0 ? 0u : ((1u << (8 * valid)) - 1u));
         v = (~v) & keep;
@@ -215,7 +210,7 @@ __device__ __forceinline__ uint32_t fg_load4(const LabelArgs &a, int y, int x, i
 // something left).  The 4096 x 4096 binary tile takes 23 us (16 MB read, 64 MB
 // written: 3.5 TB/s; 42 with a tile to a wave), a 2048 x 2048 mask, whose 1024
 // tiles leave most of the chip idle, 17 (29).  2 rows a wave: the same.
-__device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int x0, int aligned) {
+__device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int x0) {
     const int ln = lane_id();
     const int r0 = uniform((int)(threadIdx.x >> 6)) * LT_ROWS;   // the wave's first row of the tile
     const int c = 4 * ln;
@@ -225,7 +220,7 @@ __device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int
     uint32_t rows[LT_ROWS];   // all loads in flight together
 #pragma unroll
     for (int r = 0; r < LT_ROWS; ++r)
-        rows[r] = r0 + r < th ? fg_load4(a, y0 + r0 + r, x0 + c, valid, aligned) : 0u;
+        rows[r] = r0 + r < th ? fg_load4(a, y0 + r0 + r, x0 + c, valid) : 0u;
 #pragma unroll
     for (int r = 0; r < LT_ROWS; ++r) {
         const uint32_t v = rows[r];
@@ -297,7 +292,7 @@ __device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int
             const int ry = (int)(root / LT_W), rx = (int)(root % LT_W);
             ids[k] = f ? (int32_t)((int64_t)(y0 + ry) * a.pitch_lab + x0 + rx + 1) : 0;
         }
-        if (r0 + r < th) lab_store4(a.lab + (int64_t)(y0 + r0 + r) * a.pitch_lab, x0 + c, a.w, a.lab_vec, ids);
+        if (r0 + r < th) lab_store4(a.lab + (int64_t)(y0 + r0 + r) * a.pitch_lab, x0 + c, a.w, ids);
     }
     __syncthreads();
 }
@@ -305,9 +300,8 @@ __device__ void label_tile(const LabelArgs &a, RK_LDS uint32_t *par, int y0, int
 __global__ __launch_bounds__(64 * LT_WAVES) void label_local(LabelArgs a) {
     RK_LDS uint32_t *par = (RK_LDS uint32_t *)dyn_lds();
     const int n_tiles = a.tiles_x * ((a.h + LT_H - 1) / LT_H);
-    const int aligned = img_aligned(a);
     for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
-        label_tile(a, par, (tile / a.tiles_x) * LT_H, (tile % a.tiles_x) * LT_W, aligned);
+        label_tile(a, par, (tile / a.tiles_x) * LT_H, (tile % a.tiles_x) * LT_W);
 }
 
 // Phase 2: unions across tile borders.  One 64-lane workgroup per tile
@@ -347,8 +341,8 @@ __device__ void merge_tile(const LabelArgs &a, int y0, int x0) {
     int32_t ul = 0, ur = 0;                             // u[-1], u[4]
     if (y0 > 0) {
         if (x < x0 + tw) {
-            lab_load4(a.lab + (int64_t)y0 * a.pitch_lab, x, a.w, a.lab_vec, c);
-            lab_load4(a.lab + (int64_t)(y0 - 1) * a.pitch_lab, x, a.w, a.lab_vec, u);
+            lab_load4(a.lab + (int64_t)y0 * a.pitch_lab, x, a.w, c);
+            lab_load4(a.lab + (int64_t)(y0 - 1) * a.pitch_lab, x, a.w, u);
         }
         if (ln == 0) ul = at(y0 - 1, x0 - 1);
         if (ln == LANES - 1) ur = at(y0 - 1, x0 + LT_W);
@@ -418,35 +412,64 @@ __global__ void clear_words(uint32_t *p, uint32_t n) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// Phase 3: every foreground pixel takes its root's id; roots set their bit.
-// Grid-stride over (row, 256-column chunk), 64 lanes x 4 pixels.
-__global__ __launch_bounds__(64) void label_flatten(LabelArgs a) {
-    const int ln = lane_id();
-    const int chunks = (a.w + LT_W - 1) / LT_W;
-    const int64_t n = (int64_t)a.h * chunks;
-    for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
-        const int y = (int)(q / chunks), x0 = (int)(q % chunks) * LT_W;
-        int32_t *row = a.lab + (int64_t)y * a.pitch_lab;
-        const int xl = x0 + 4 * ln;
-        int32_t v[4];
-        lab_load4(row, xl, a.w, a.lab_vec, v);
-        bool any = false;
-        int32_t last_v = 0, last_r = 0;   // (a lane's pixels mostly share a tile root)
-        for (int k = 0; k < 4; ++k) {
-            if (v[k] == 0) continue;
-            const int32_t root = v[k] == last_v ? last_r : g_root(a.lab, v[k]);
-            last_v = v[k];
-            last_r = root;
-            any |= root != v[k];
-            v[k] = root;
-            const int32_t self = (int32_t)((int64_t)y * a.pitch_lab + xl + k + 1);
-            if (root == self && a.bits) {
-                const uint32_t bit = (uint32_t)(self - 1);
-                __hip_atomic_fetch_or(a.bits + (bit >> 5), 1u << (bit & 31u), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
-            }
+// The kernels below go over the label plane in units of LF_ROWS rows of 256
+// columns, a wave per unit (64 lanes x 4 pixels a row, the rows' loads out
+// together; a row per wave took 81 us against 76 for the labelling of the
+// 4096 x 4096 binary tile, each of its last passes moving 128 MB).
+constexpr int LF_ROWS = 4;
+
+__device__ __forceinline__ int64_t lf_units(int h, int w) {
+    return (int64_t)((h + LF_ROWS - 1) / LF_ROWS) * ((w + LT_W - 1) / LT_W);
+}
+
+struct LfUnit {
+    int y0, rows, x;   // first row, rows inside the image, the lane's first column
+    __device__ __forceinline__ LfUnit(int64_t q, int h, int w) {
+        const int chunks = (w + LT_W - 1) / LT_W;
+        y0 = (int)(q / chunks) * LF_ROWS;
+        rows = min(LF_ROWS, h - y0);
+        x = (int)(q % chunks) * LT_W + 4 * lane_id();
+    }
+    __device__ __forceinline__ void load(const int32_t *lab, int64_t pitch, int w, int32_t v[LF_ROWS][4]) const {
+#pragma unroll
+        for (int r = 0; r < LF_ROWS; ++r) {
+            v[r][0] = v[r][1] = v[r][2] = v[r][3] = 0;
+            if (r < rows) lab_load4(lab + (int64_t)(y0 + r) * pitch, x, w, v[r]);
         }
-        if (any) lab_store4(row, xl, a.w, a.lab_vec, v);
+    }
+};
+
+// Phase 3: every foreground pixel takes its root's id; roots set their bit.
+// Grid-stride over the units.
+__global__ __launch_bounds__(64) void label_flatten(LabelArgs a) {
+    const int64_t n = lf_units(a.h, a.w);
+    for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
+        const LfUnit u(q, a.h, a.w);
+        int32_t v[LF_ROWS][4];
+        u.load(a.lab, a.pitch_lab, a.w, v);
+        int32_t last_v = 0, last_r = 0;   // (a lane's pixels mostly share a tile root)
+#pragma unroll
+        for (int r = 0; r < LF_ROWS; ++r) {
+            int32_t *row = a.lab + (int64_t)(u.y0 + r) * a.pitch_lab;
+            bool any = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (v[r][k] == 0) continue;
+                if (v[r][k] != last_v) {
+                    last_v = v[r][k];
+                    last_r = g_root(a.lab, last_v);
+                }
+                any |= last_r != v[r][k];
+                v[r][k] = last_r;
+                const int32_t self = (int32_t)((int64_t)(u.y0 + r) * a.pitch_lab + u.x + k + 1);
+                if (last_r == self && a.bits) {
+                    const uint32_t bit = (uint32_t)(self - 1);
+                    __hip_atomic_fetch_or(a.bits + (bit >> 5), 1u << (bit & 31u), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            if (any) lab_store4(row, u.x, a.w, v[r]);
+        }
     }
 }
 
@@ -508,25 +531,31 @@ __global__ __launch_bounds__(64) void rank_words(LabelArgs a) {
     }
 }
 
-// Phase 5: final labels 1..n in raster order of the roots.
+// Phase 5: final labels 1..n in raster order of the roots.  Grid-stride over
+// the units.
 __global__ __launch_bounds__(64) void label_final(LabelArgs a) {
-    const int ln = lane_id();
-    const int chunks = (a.w + LT_W - 1) / LT_W;
-    const int64_t n = (int64_t)a.h * chunks;
+    const int64_t n = lf_units(a.h, a.w);
     for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
-        const int y = (int)(q / chunks), x0 = (int)(q % chunks) * LT_W;
-        int32_t *row = a.lab + (int64_t)y * a.pitch_lab;
-        const int xl = x0 + 4 * ln;
-        int32_t v[4];
-        lab_load4(row, xl, a.w, a.lab_vec, v);
-        if ((v[0] | v[1] | v[2] | v[3]) == 0) continue;
-        for (int k = 0; k < 4; ++k) {
-            if (v[k] == 0) continue;
-            const uint32_t r = (uint32_t)(v[k] - 1);
-            const uint32_t below = a.bits[r >> 5] & ((1u << (r & 31u)) - 1u);
-            v[k] = (int32_t)(a.word_off[r >> 5] + (uint32_t)__popc(below) + 1u);
+        const LfUnit u(q, a.h, a.w);
+        int32_t v[LF_ROWS][4];
+        u.load(a.lab, a.pitch_lab, a.w, v);
+        int32_t last_v = 0, last_l = 0;
+#pragma unroll
+        for (int r = 0; r < LF_ROWS; ++r) {
+            if ((v[r][0] | v[r][1] | v[r][2] | v[r][3]) == 0) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (v[r][k] == 0) continue;
+                if (v[r][k] != last_v) {
+                    last_v = v[r][k];
+                    const uint32_t root = (uint32_t)(last_v - 1);
+                    const uint32_t below = a.bits[root >> 5] & ((1u << (root & 31u)) - 1u);
+                    last_l = (int32_t)(a.word_off[root >> 5] + (uint32_t)__popc(below) + 1u);
+                }
+                v[r][k] = last_l;
+            }
+            lab_store4(a.lab + (int64_t)(u.y0 + r) * a.pitch_lab, u.x, a.w, v[r]);
         }
-        lab_store4(row, xl, a.w, a.lab_vec, v);
     }
 }
 
@@ -536,59 +565,62 @@ __global__ __launch_bounds__(64) void label_final(LabelArgs a) {
 struct AreaArgs {
     const int32_t *lab;
     int64_t pitch_lab;
-    int32_t lab_vec;
     uint32_t *area;         // pixel count per root id (index 0 unused)
     uint8_t *out;           // the image, overwritten with 255 / 0
     int64_t pitch_out;
-    int32_t out_aligned;    // 1: the image allows dword accesses
     int32_t h, w;
     int64_t min_area, max_area;
 };
 
-// Pixel counts per root id: runs of equal ids inside a lane's 4 pixels are
-// added with one atomic each.
+// Pixel counts per root id: equal ids that follow one another in a lane's pixels
+// are added with one atomic.  Grid-stride over the units.
 __global__ __launch_bounds__(64) void area_count(AreaArgs a) {
-    const int ln = lane_id();
-    const int chunks = (a.w + LT_W - 1) / LT_W;
-    const int64_t n = (int64_t)a.h * chunks;
+    const int64_t n = lf_units(a.h, a.w);
     for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
-        const int y = (int)(q / chunks), x0 = (int)(q % chunks) * LT_W;
-        const int32_t *row = a.lab + (int64_t)y * a.pitch_lab;
-        int32_t vv[4];
-        lab_load4(row, x0 + 4 * ln, a.w, a.lab_vec, vv);
+        const LfUnit u(q, a.h, a.w);
+        int32_t v[LF_ROWS][4];
+        u.load(a.lab, a.pitch_lab, a.w, v);
         int32_t cur = 0;
         uint32_t run = 0;
-        for (int k = 0; k < 4; ++k) {
-            const int32_t v = vv[k];
-            if (v != cur) {
-                if (cur != 0) __hip_atomic_fetch_add(a.area + cur, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                cur = v;
-                run = 0;
+#pragma unroll
+        for (int r = 0; r < LF_ROWS; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (v[r][k] == 0) continue;
+                if (v[r][k] != cur) {
+                    if (cur != 0) __hip_atomic_fetch_add(a.area + cur, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cur = v[r][k];
+                    run = 0;
+                }
+                run += 1;
             }
-            run += 1;
-        }
         if (cur != 0) __hip_atomic_fetch_add(a.area + cur, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 __global__ __launch_bounds__(64) void area_apply(AreaArgs a) {
-    const int ln = lane_id();
-    const int chunks = (a.w + LT_W - 1) / LT_W;
-    const int64_t n = (int64_t)a.h * chunks;
+    const int64_t n = lf_units(a.h, a.w);
     for (int64_t q = blockIdx.x; q < n; q += gridDim.x) {
-        const int y = (int)(q / chunks), x0 = (int)(q % chunks) * LT_W;
-        const int32_t *row = a.lab + (int64_t)y * a.pitch_lab;
-        uint8_t *orow = a.out + (int64_t)y * a.pitch_out;
-        const int xl = x0 + 4 * ln;
-        int32_t vv[4];
-        lab_load4(row, xl, a.w, a.lab_vec, vv);
-        uint32_t out = 0;
-        for (int k = 0; k < 4; ++k) {
-            const int32_t v = vv[k];
-            const int64_t ar = v != 0 ? (int64_t)a.area[v] : -1;
-            if (v != 0 && ar >= a.min_area && ar <= a.max_area) out |= 0xffu << (8 * k);
+        const LfUnit u(q, a.h, a.w);
+        int32_t v[LF_ROWS][4];
+        u.load(a.lab, a.pitch_lab, a.w, v);
+        int32_t last_v = 0;
+        uint32_t keep = 0;
+#pragma unroll
+        for (int r = 0; r < LF_ROWS; ++r) {
+            uint32_t out = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (v[r][k] == 0) continue;
+                if (v[r][k] != last_v) {
+                    last_v = v[r][k];
+                    const int64_t ar = (int64_t)a.area[last_v];
+                    keep = ar >= a.min_area && ar <= a.max_area ? 0xffu : 0u;
+                }
+                out |= keep << (8 * k);
+            }
+            if (r < u.rows) gstore4(a.out + (int64_t)(u.y0 + r) * a.pitch_out, u.x, min(4, a.w - u.x), out);
         }
-        gstore4(orow, xl, min(4, a.w - xl), a.out_aligned, out);
     }
 }
 

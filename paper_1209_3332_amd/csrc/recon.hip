@@ -1298,9 +1298,8 @@ static int enqueue_label(const recon_image &img, int32_t *lab, int64_t pitch_lab
     a.word_off = (uint32_t *)(area + round_up((size_t)a.n_words * 4, 256));
     a.seg_sum = (uint32_t *)(area + 2 * round_up((size_t)a.n_words * 4, 256));
     a.count = count;
-    a.lab_vec = (((uintptr_t)lab | (uintptr_t)(pitch_lab * 4)) & 15u) == 0 ? 1 : 0;
     const int64_t n_tiles = (int64_t)a.tiles_x * ((img.height + rk::LT_H - 1) / rk::LT_H);
-    const int64_t n_rows = (int64_t)img.height * a.tiles_x;
+    const int64_t n_rows = (int64_t)((img.height + rk::LF_ROWS - 1) / rk::LF_ROWS) * a.tiles_x;
     const int g_tiles = (int)std::min<int64_t>(n_tiles, 65535);
     const int g_rows = (int)std::min<int64_t>(n_rows, 65535);
     const int g_segs = (int)std::min<uint32_t>(a.n_segs, 65535u);
@@ -1365,8 +1364,6 @@ int recon_area_threshold(recon_ctx *ctx, recon_image *img, int conn, int64_t min
     rk::AreaArgs a{};
     a.lab = lab;
     a.pitch_lab = pitch_lab;
-    a.lab_vec = (((uintptr_t)lab | (uintptr_t)(pitch_lab * 4)) & 15u) == 0 ? 1 : 0;
-    a.out_aligned = aligned4(img->data, img->pitch) ? 1 : 0;
     a.area = area;
     a.out = img->data;
     a.pitch_out = img->pitch;
@@ -1374,7 +1371,7 @@ int recon_area_threshold(recon_ctx *ctx, recon_image *img, int conn, int64_t min
     a.w = img->width;
     a.min_area = min_area;
     a.max_area = max_area;
-    const int64_t n_rows = (int64_t)img->height * ((img->width + rk::LT_W - 1) / rk::LT_W);
+    const int64_t n_rows = (int64_t)((img->height + rk::LF_ROWS - 1) / rk::LF_ROWS) * ((img->width + rk::LT_W - 1) / rk::LT_W);
     const int g_rows = (int)std::min<int64_t>(n_rows, 65535);
     hipLaunchKernelGGL(rk::clear_words, dim3((unsigned)std::min<size_t>((n_area + 255) / 256, 4096)), dim3(256), 0,
                        s, area, (uint32_t)n_area);

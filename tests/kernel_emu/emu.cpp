@@ -305,7 +305,6 @@ static int emu_label(const uint8_t *img_in, int h, int w, int conn, int n_waves,
     a.seg_sum = (uint32_t *)std::malloc(a.n_segs * 4);
     int32_t count = -1;
     a.count = &count;
-    a.lab_vec = (((uintptr_t)lab | (uintptr_t)(pitch_lab * 4)) & 15u) == 0 ? 1 : 0;
     auto serial = [&](auto fn, uint32_t blocks, uint32_t threads) {
         kemu::gridDim_.x = blocks;
         kemu::blockDim_.x = threads;
@@ -348,8 +347,6 @@ static int emu_label(const uint8_t *img_in, int h, int w, int conn, int n_waves,
         AreaArgs b{};
         b.lab = lab;
         b.pitch_lab = pitch_lab;
-        b.lab_vec = a.lab_vec;
-        b.out_aligned = (((uintptr_t)img.data() | (uintptr_t)pitch_img) & 3u) == 0 ? 1 : 0;
         b.area = area;
         b.out = img.data();
         b.pitch_out = pitch_img;
