@@ -103,7 +103,6 @@ template <int BH>
 __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, KArgs a) {
     if (a.work->classify_skip == seq_of(tt)) return;   // the samples decided every route
     const int ln = lane_id(), wv = uniform((int)(threadIdx.x >> 6));
-    RK_LDS uint32_t *wrote_wv = (RK_LDS uint32_t *)dyn_lds();   // per wave: it changed a route word or has_grey
     constexpr int UH = BH < 32 ? BH : 32;         // rows of a unit
     constexpr int CH = UH / CLASS_WAVES;          // rows of a wave, their loads in flight together
     constexpr int PER = BH / UH;
@@ -113,7 +112,6 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
     uint32_t acc_or = 0, acc_and = 0xffffffffu;   // four bytes side by side
     uint32_t seen_or = 0, seen_and = 0;           // its words as read last
     const uint32_t seq = seq_of(tt);
-    bool wrote = false;
     auto flush = [&]() {
         if (acc_k < 0) return;
         acc_or |= acc_or >> 16;
@@ -128,13 +126,13 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
             uint32_t *wo = a.route + ROUTE_WORDS * acc_k, *wa = wo + 1;
             if ((acc_or & ~seen_or) != 0u) __hip_atomic_fetch_or(wo, acc_or, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((seen_and & ~acc_and) != 0u) __hip_atomic_fetch_and(wa, acc_and, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wrote = true;
             // (read back after both: of the waves that make a task grey together, the last one sees it)
             const uint32_t no = __hip_atomic_load(wo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t na = __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // this task is grey (any writer, same value; a plain load first so
             // that a line already holding it is not written again by every wave)
-            if (no != 0u && no != na && a.work->has_grey != seq) a.work->has_grey = seq;
+            if (no != 0u && no != na && a.work->has_grey != seq)
+                __hip_atomic_store(&a.work->has_grey, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         acc_or = 0;
         acc_and = 0xffffffffu;
@@ -171,21 +169,16 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
         }
     }
     flush();
-    // the last workgroup to finish decides every task's route (decide_tasks):
-    // a workgroup that wrote releases its writes with its count, and the last
-    // one acquires them all (an agent-scope release or acquire writes back or
-    // invalidates this XCD's L2, so the others neither fence nor acquire)
-    if (ln == 0) wrote_wv[wv] = wrote ? 1u : 0u;
+    // the last workgroup to finish decides every task's route (decide_tasks).
+    // All writes above are at the device-coherent level, and every wave waits
+    // for its own before its workgroup counts (a barrier alone waits for LDS
+    // only), so the count needs no release of this XCD's L2
+    vm_sync();
     __syncthreads();
     if (wv != 0) return;
     uint32_t prior = 0;
-    if (ln == 0) {
-        uint32_t any = 0;
-        for (int v = 0; v < CLASS_WAVES; ++v) any |= wrote_wv[v];
-        uint32_t *cnt = &a.work->classify_done;
-        prior = any ? __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT)
-                    : __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (ln == 0)
+        prior = __hip_atomic_fetch_add(&a.work->classify_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (uniform(prior) + 1u == gridDim.x) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         decide_tasks(tt, a);

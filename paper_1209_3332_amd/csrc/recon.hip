@@ -503,7 +503,7 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         case kRegionSmallV: hipLaunchKernelGGL(rk::K<64>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break; \
         default: hipLaunchKernelGGL(rk::K<kUnitRows[kRegionV]>, dim3(GRID), dim3(THREADS), LDS, s, tt, ka); break; \
     }
-        RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 64 * rk::CLASS_WAVES, 4 * rk::CLASS_WAVES);
+        RK_COMP(comp_classify, (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * std::max(1, bh / 32), 1024)), 64 * rk::CLASS_WAVES, 0);
         // A large batch (a replayed graph) forks: the ring and marker planes
         // (prepare) and the revisit kernel of the tasks that keep the block
         // route go to the second stream, while the route's labelling and

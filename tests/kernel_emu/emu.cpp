@@ -631,7 +631,7 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
 #undef KEMU_PICK
             bad += workgroups(n_waves, wg_waves, lds_sz, body);
         };
-        comp_grid(0, 4 * CLASS_WAVES, CLASS_WAVES);   // the classification; its last workgroup decides the routes
+        comp_grid(0, 0, CLASS_WAVES);   // the classification; its last workgroup decides the routes
         grid_run([&] { prepare(tt, ka, any_mapped ? 1 : 0); }, 8, 64);
         comp_grid(1, (size_t)LT_H * LT_W * 4, LT_WAVES);
         comp_grid(2, 0);
