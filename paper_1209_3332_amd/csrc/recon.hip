@@ -260,9 +260,9 @@ void drop_graphs(recon_ctx *c) {
 }
 
 // Grow the workspace to hold n_tasks tasks, n_blocks blocks and `area_bytes`
-// bytes of scratch planes.  Growing synchronises the device and drops the
-// captured graphs (they hold the old pointers).
-int ensure_capacity(recon_ctx *c, size_t n_tasks, size_t n_blocks, size_t area_bytes) {
+// bytes of scratch planes, for a launch on `stream`.  Growing synchronises the
+// device and drops the captured graphs (they hold the old pointers).
+int ensure_capacity(recon_ctx *c, size_t n_tasks, size_t n_blocks, size_t area_bytes, hipStream_t stream) {
     if (n_tasks <= c->cap_tasks && n_blocks <= c->cap_blocks && area_bytes <= c->cap_scratch)
         return RECON_OK;
     HIP_TRY(hipDeviceSynchronize());
@@ -287,8 +287,15 @@ int ensure_capacity(recon_ctx *c, size_t n_tasks, size_t n_blocks, size_t area_b
                     nt, nb, ns);
     }
     // the scheduler words start at 0: the flags keyed by a launch number must
-    // not find a stale number that some earlier owner of this memory left
-    HIP_TRY(hipMemset(c->d_work, 0, sizeof(rk::Work)));
+    // not find a stale number that some earlier owner of this memory left.
+    // Cleared by a kernel on the launch's own stream: hipMemset returns before
+    // it has happened, behind whatever is queued on the null stream by then, and
+    // a non-blocking stream does not wait for that one -- it would zero the
+    // counters of a launch at work.
+    static_assert(sizeof(rk::Work) % 4 == 0, "cleared by words");
+    hipLaunchKernelGGL(rk::clear_words, dim3(1), dim3(256), 0, stream, (uint32_t *)c->d_work,
+                       (uint32_t)(sizeof(rk::Work) / 4));
+    HIP_TRY(hipGetLastError());
     c->cap_tasks = nt;
     c->cap_blocks = nb;
     c->cap_scratch = ns;
@@ -599,7 +606,7 @@ int run_tasks(recon_ctx *c, const recon_task *tasks, int n, hipStream_t stream, 
     const bool with_route = c->cfg.component_route >= 0 && c->cfg.stop_after_stage == 0;
     build_table(c->cfg, tasks, n, bh, table, uses_scratch, total_blocks, scratch_need, any_mapped, with_route,
                 lab_off);
-    rc = ensure_capacity(c, (size_t)n, (size_t)total_blocks, scratch_need);
+    rc = ensure_capacity(c, (size_t)n, (size_t)total_blocks, scratch_need, stream);
     if (rc) return rc;
     for (int k = 0; k < n; ++k) {
         rk::TaskDev &d = table[k];
@@ -1333,7 +1340,7 @@ int recon_label(recon_ctx *ctx, const recon_image *img, int32_t *labels, int64_t
     uint32_t nw = 0, ns = 0;
     size_t bytes = 0;
     label_layout(img->height, img->width, label_pitch, nw, ns, bytes);
-    rc = ensure_capacity(ctx, 0, 0, bytes);
+    rc = ensure_capacity(ctx, 0, 0, bytes, (hipStream_t)stream);
     if (rc) return rc;
     return enqueue_label(*img, labels, label_pitch, conn, count, ctx->d_scratch, true, (hipStream_t)stream);
 }
@@ -1354,7 +1361,7 @@ int recon_area_threshold(recon_ctx *ctx, recon_image *img, int conn, int64_t min
     const size_t plane = round_up((size_t)img->height * (size_t)pitch_lab * 4, 256);
     const size_t n_area = (size_t)img->height * (size_t)pitch_lab + 1;
     const size_t abytes = round_up(n_area * 4, 256);
-    rc = ensure_capacity(ctx, 0, 0, plane + abytes);
+    rc = ensure_capacity(ctx, 0, 0, plane + abytes, (hipStream_t)stream);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     int32_t *lab = (int32_t *)ctx->d_scratch;
@@ -1420,7 +1427,7 @@ int recon_distance(recon_ctx *ctx, const recon_image *img, int32_t *dist2, int64
     if (plane_overlaps(*img, dist2, dist_pitch)) return fail(RECON_EINVAL, "distance plane and image overlap");
     rc = ensure_device(ctx);
     if (rc) return rc;
-    rc = ensure_capacity(ctx, 0, 0, edt_summary_bytes(img->height, img->width));
+    rc = ensure_capacity(ctx, 0, 0, edt_summary_bytes(img->height, img->width), (hipStream_t)stream);
     if (rc) return rc;
     rk::EdtArgs a{};
     a.img = img->data;
@@ -1442,7 +1449,7 @@ int recon_pre_watershed(recon_ctx *ctx, recon_image *img, int conn, void *stream
     if (rc) return rc;
     const int64_t pitch_g = (int64_t)round_up((size_t)img->width, 64);
     const size_t plane = round_up((size_t)img->height * (size_t)pitch_g * 4, 256);
-    rc = ensure_capacity(ctx, 0, 0, plane + edt_summary_bytes(img->height, img->width));
+    rc = ensure_capacity(ctx, 0, 0, plane + edt_summary_bytes(img->height, img->width), (hipStream_t)stream);
     if (rc) return rc;
     rk::EdtArgs a{};
     a.img = img->data;
