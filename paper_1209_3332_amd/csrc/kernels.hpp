@@ -179,8 +179,9 @@ struct KArgs {
 
 // Route words of a task: [0] OR and [1] AND of its nonzero mask values (the
 // component route's classification), [2] the ring position of its first block,
-// [3] 1 if the task takes the component route (decided by queue_tasks),
-// [4] 1 if its sampled foreground is thin (runs of at most ~32 pixels on average).
+// [3] 1 if the task takes the component route (decided by decide_tasks),
+// [4] 1 if its sampled foreground is thin (runs of at most ~32 pixels on average),
+// [5] 1 if decide_tasks found its mask two-valued.
 constexpr int ROUTE_WORDS = 8;
 
 // ---------------------------------------------------------------------------
@@ -1964,7 +1965,10 @@ __device__ void decide_tasks(const TaskTable &tt, const KArgs &a) {
     // sum of the steps before), the tasks whose mask looks two-valued first.
     // Most of their blocks have nothing to do before a flood reaches them, so
     // their first visits are short, and the flood, a chain of visits, starts
-    // beside the other tasks' work instead of after it.
+    // beside the other tasks' work instead of after it.  Each task is decided
+    // once, in the first pass, and the second one goes by what that wrote: a
+    // task judged anew there could be counted twice (the launch would never
+    // drain) or not at all.
     uint32_t base = 0;
     bool any_route = false;
     for (int pass = 0; pass < 2; ++pass)
@@ -1975,14 +1979,21 @@ __device__ void decide_tasks(const TaskTable &tt, const KArgs &a) {
             if (i < n_tasks) {
                 const TaskDev t = task_of(tt, (int)i);
                 uint32_t *rw = a.route + ROUTE_WORDS * i;
-                const uint32_t o = __hip_atomic_load(rw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint32_t an = __hip_atomic_load(rw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint32_t thin = __hip_atomic_load(rw + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const bool two = o == 0u || o == an;
-                take = t.lab && two && (a.route_policy == 1 || !grey_work || thin != 0u);
+                bool two;
+                if (pass == 0) {   // decided here, once
+                    const uint32_t o = __hip_atomic_load(rw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const uint32_t an = __hip_atomic_load(rw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const uint32_t thin = __hip_atomic_load(rw + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    two = o == 0u || o == an;
+                    take = t.lab && two && (a.route_policy == 1 || !grey_work || thin != 0u);
+                    rw[3] = take ? 1u : 0u;
+                    rw[5] = two ? 1u : 0u;
+                } else {           // (the same lane's words)
+                    take = rw[3] != 0u;
+                    two = rw[5] != 0u;
+                }
                 mine = two == (pass == 0);
                 if (mine) {
-                    rw[3] = take ? 1u : 0u;
                     if (take) a.tile_done[i] = 1u;
                     else nb = (uint32_t)(t.nby * t.nbx);
                 }

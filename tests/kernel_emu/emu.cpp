@@ -683,12 +683,94 @@ int emu_run(const EmuTask *tasks, int n, int bh, int qcap, int scan_rounds, int 
 
 }  // extern "C"
 
+// decide_tasks while the route words it reads keep changing (a thread turns masks
+// from two-valued to grey and back): whatever it reads, every task is either on the
+// component route or owns one range of ring positions, the ranges lie end to end and
+// their sum is what the launch counts as outstanding.  The number of runs that
+// broke this.
+static int emu_decide(int n, int reps, unsigned seed) {
+    using namespace rk;
+    std::vector<uint8_t> mem(sizeof(BatchHdr) + n * sizeof(TaskDev));
+    TaskDev *table = (TaskDev *)(mem.data() + sizeof(BatchHdr));
+    int32_t plane = 0;
+    uint32_t total = 0;
+    for (int k = 0; k < n; ++k) {
+        seed = seed * 1664525u + 1013904223u;
+        table[k] = TaskDev{};
+        table[k].nby = 1 + (int)(seed >> 28);
+        table[k].nbx = 1 + (int)((seed >> 24) & 3u);
+        table[k].block0 = total;
+        table[k].lab = (seed >> 20) & 3u ? &plane : nullptr;
+        total += (uint32_t)(table[k].nby * table[k].nbx);
+    }
+    BatchHdr *hdr = (BatchHdr *)mem.data();
+    *hdr = BatchHdr{};
+    hdr->n_tasks = (uint32_t)n;
+    hdr->total_blocks = total;
+    hdr->launch_seq = 7;
+    TaskTable tt{};
+    tt.hdr = hdr;
+    tt.ext = table;
+    std::vector<uint32_t> route((size_t)ROUTE_WORDS * n), pend(n), done(n);
+    int broken = 0;
+    for (int rep = 0; rep < reps; ++rep) {
+        Work work{};
+        KArgs a{};
+        a.work = &work;
+        a.tile_pending = pend.data();
+        a.tile_done = done.data();
+        a.route = route.data();
+        a.route_policy = rep & 1;
+        work.has_grey = rep & 2 ? 7u : 0u;
+        for (int k = 0; k < n; ++k) {
+            uint32_t *rw = &route[(size_t)ROUTE_WORDS * k];
+            for (int q = 0; q < ROUTE_WORDS; ++q) rw[q] = 0u;
+            rw[0] = rw[1] = 200u;
+            rw[4] = (uint32_t)k & 1u;
+            pend[k] = done[k] = 0u;
+        }
+        std::atomic<bool> stop{false};
+        std::thread turn([&] {
+            for (uint32_t v = 0; !stop; ++v)
+                for (int k = 0; k < n; ++k)
+                    __atomic_store_n(&route[(size_t)ROUTE_WORDS * k], (v + (uint32_t)k) & 1u ? 200u : 255u, __ATOMIC_RELAXED);
+        });
+        const bool ran = kemu::run_wave([&] { decide_tasks(tt, a); }, 16);
+        stop = true;
+        turn.join();
+        std::vector<int> owner(total, 0);
+        uint32_t sum = 0;
+        bool ok = ran, any = false;
+        for (int k = 0; k < n; ++k) {
+            const uint32_t *rw = &route[(size_t)ROUTE_WORDS * k], nb = (uint32_t)(table[k].nby * table[k].nbx);
+            if (rw[3]) {
+                any = true;
+                ok = ok && table[k].lab && done[k] == 1u && pend[k] == 0u;
+                continue;
+            }
+            sum += nb;
+            ok = ok && done[k] == 0u && pend[k] == nb && rw[2] + nb <= total;
+            for (uint32_t q = 0; ok && q < nb; ++q) ok = ++owner[rw[2] + q] == 1;
+        }
+        for (uint32_t q = 0; ok && q < sum; ++q) ok = owner[q] == 1;
+        ok = ok && work.pending == sum && work.ring_tail == sum && (work.route_any == 7u) == any;
+        broken += !ok;
+    }
+    return broken;
+}
+
 #ifdef KEMU_MAIN
 // Stand-alone driver (lets the sanitizer runtime link into the executable):
 //   kemu <bh> <qcap> <scan_rounds> <waves> <watchdog_s> <n> then n lines of
 //   "op conn hval h w image_path mask_path_or_- out_path" on stdin.
 #include <string>
 int main(int argc, char **argv) {
+    //   kemu decide <tasks> <runs> <seed>
+    if (argc == 5 && std::string(argv[1]) == "decide") {
+        const int broken = emu_decide(std::atoi(argv[2]), std::atoi(argv[3]), (unsigned)std::atoi(argv[4]));
+        std::printf("broken %d\n", broken);
+        return broken == 0 ? 0 : 1;
+    }
     //   kemu label <conn> <h> <w> <waves> <min_area> <max_area> <image_path> <labels_out> <area_out>
     if (argc == 11 && std::string(argv[1]) == "label") {
         const int conn = std::atoi(argv[2]), h = std::atoi(argv[3]), w = std::atoi(argv[4]);
