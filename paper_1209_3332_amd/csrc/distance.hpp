@@ -17,9 +17,7 @@
 //             column of one segment: it holds the segment's pixels in
 //             registers, takes the nearest 0 above and below the segment from
 //             the other segments' summaries (the nearest segment that has
-//             one), scans down and up and writes g once, as 16-bit values
-//             packed into the first half of the row's 32-bit elements (distances
-//             stay below 16384; half the bytes to write and to read back).
+//             one), scans down and up and writes g once.
 //   edt_rows  one workgroup per row: the row of g is staged in LDS, then
 //             every pixel takes min over x' of (x - x')^2 + g(x')^2,
 //             searched outward from x and stopped once (x - x')^2 alone
@@ -34,7 +32,6 @@
 namespace rk {
 
 constexpr int32_t EDT_NONE = 0x3fffffff;   // no 0 pixel in the column
-constexpr uint32_t EDT_NONE16 = 0xffffu;    // the same in 16 bits (a column distance is below the height, at most 16384)
 constexpr uint32_t EDT_FAR = 0x7fffffffu;   // no 0 pixel (any squared distance is below 2^30)
 constexpr int EDT_SEG = 16;                // rows per column segment (held in registers)
 constexpr int EDT_MAX_W = 16384;           // widest row staged in LDS
@@ -42,8 +39,8 @@ constexpr int EDT_MAX_W = 16384;           // widest row staged in LDS
 struct EdtArgs {
     const uint8_t *img;    // input (0 = background)
     int64_t pitch_img;     // bytes
-    int32_t *g;            // rows of 16-bit column distances, then (mode 0) dist2 in place
-    int64_t pitch_g;       // 32-bit elements
+    int32_t *g;            // column distances, then (mode 0) dist2 in place
+    int64_t pitch_g;       // elements
     uint8_t *d8;           // mode 1: D8 output (may be the input image)
     int64_t pitch_d8;      // bytes
     int32_t h, w;
@@ -104,19 +101,18 @@ __global__ void edt_zeros(EdtArgs a) {
     }
 }
 
-__device__ __forceinline__ uint32_t edt_half(int32_t g) { return g == EDT_NONE ? EDT_NONE16 : (uint32_t)g; }
-typedef uint32_t u32x2 __attribute__((vector_size(8)));   // one 8-byte access
+typedef int32_t i32x4 __attribute__((vector_size(16)));   // one 16-byte access
 
 // Column pass.  Grid-stride over (segment, column) with consecutive threads on
-// consecutive columns (coalesced byte loads and 16-bit stores); with dword-
+// consecutive columns (coalesced byte loads and int32 stores); with dword-
 // aligned image rows a thread takes 4 adjacent columns at once (dword loads,
-// and 8-byte stores where the distance plane allows them).
+// and 16-byte stores where the distance plane allows them).
 __global__ void edt_cols(EdtArgs a) {
     const int n_seg = (a.h + EDT_SEG - 1) / EDT_SEG;
     if (((((uintptr_t)a.img) | (uintptr_t)a.pitch_img | (uintptr_t)a.w) & 3u) == 0) {
         const int w4 = a.w / 4;
         const int64_t n4 = (int64_t)n_seg * w4;
-        const bool vec = ((((uintptr_t)a.g) | (uintptr_t)(a.pitch_g * 4)) & 7u) == 0;
+        const bool vec = ((((uintptr_t)a.g) | (uintptr_t)(a.pitch_g * 4)) & 15u) == 0;
         for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n4; q += (int64_t)gridDim.x * blockDim.x) {
             const int x = (int)(q % w4) * 4;
             const int s = (int)(q / w4);
@@ -164,13 +160,12 @@ __global__ void edt_cols(EdtArgs a) {
 #pragma unroll
             for (int r = 0; r < EDT_SEG; ++r) {
                 if (y0 + r >= a.h) continue;
-                uint16_t *row = (uint16_t *)(a.g + (int64_t)(y0 + r) * a.pitch_g) + x;
+                int32_t *row = a.g + (int64_t)(y0 + r) * a.pitch_g + x;
                 if (vec) {
-                    *(RK_GLOBAL u32x2 *)row = u32x2{edt_half(g[r][0]) | edt_half(g[r][1]) << 16,
-                                                    edt_half(g[r][2]) | edt_half(g[r][3]) << 16};
+                    *(RK_GLOBAL i32x4 *)row = i32x4{g[r][0], g[r][1], g[r][2], g[r][3]};
                 } else {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) ((RK_GLOBAL uint16_t *)row)[c] = (uint16_t)edt_half(g[r][c]);
+                    for (int c = 0; c < 4; ++c) ((RK_GLOBAL int32_t *)row)[c] = g[r][c];
                 }
             }
         }
@@ -218,10 +213,10 @@ __global__ void edt_cols(EdtArgs a) {
             else if (r < last && d != EDT_NONE) d += 1;
             if (d < g[r]) g[r] = d;
         }
-        RK_GLOBAL uint16_t *gc = (RK_GLOBAL uint16_t *)a.g + x;
+        RK_GLOBAL int32_t *gc = (RK_GLOBAL int32_t *)a.g + x;
 #pragma unroll
         for (int r = 0; r < EDT_SEG; ++r)
-            if (y0 + r < a.h) gc[(int64_t)(y0 + r) * a.pitch_g * 2] = (uint16_t)edt_half(g[r]);
+            if (y0 + r < a.h) gc[(int64_t)(y0 + r) * a.pitch_g] = g[r];
     }
 }
 
@@ -256,6 +251,10 @@ __device__ __forceinline__ uint32_t isqrt_cap255(uint32_t v) {
 constexpr int EDT_ANCHOR = 256;
 constexpr int EDT_TRY = 64;          // outward steps tried before a pixel is left over
 constexpr int EDT_MAX_PER_THREAD = 64;   // pixels per thread and row (16384 / 256); a mask bit each
+
+// In LDS a column distance takes 16 bits (it is below the height, at most
+// 16384); EDT_NONE16 marks a column without a 0 pixel.
+constexpr uint32_t EDT_NONE16 = 0xffffu;
 
 // Squared distances stay below 2^30 (both coordinates below 16384), so 32 bits
 // hold them; EDT_FAR is above all of them.
@@ -326,12 +325,9 @@ __global__ void edt_rows(EdtArgs a) {
     int it = 0;
     for (int y = blockIdx.x; y < a.h; y += gridDim.x, ++it) {
         RK_GLOBAL int32_t *gr = (RK_GLOBAL int32_t *)a.g + (int64_t)y * a.pitch_g;
-        {   // the row's 16-bit values, two at a time
-            const RK_GLOBAL uint32_t *src = (const RK_GLOBAL uint32_t *)gr;
-            for (int x = 2 * threadIdx.x; x < w; x += 2 * blockDim.x) {
-                if (x + 1 < w) *(RK_LDS uint32_t *)(row + x) = src[x >> 1];
-                else row[x] = ((const RK_GLOBAL uint16_t *)gr)[x];
-            }
+        for (int x = threadIdx.x; x < w; x += blockDim.x) {
+            const int32_t v = gr[x];
+            row[x] = (uint16_t)(v == EDT_NONE ? EDT_NONE16 : (uint32_t)v);
         }
         __syncthreads();
         if (may_leave && threadIdx.x == 0) left_over[(it + 1) & 1] = 0;

@@ -370,7 +370,25 @@ static int emu_label(const uint8_t *img_in, int h, int w, int conn, int n_waves,
 // ---------------------------------------------------------------------------
 // distance-transform driver: mode 0 writes dist2 (int32), mode 1 D8 (uint8)
 
-static int emu_edt(const uint8_t *img_in, int h, int w, int mode, int n_waves, int32_t *d2_out, uint8_t *d8_out) {
+// The capped root of every squared distance below 2^17, and of those around each
+// square up to the largest a plane can hold, against the definition: how many differ.
+static long emu_root(void) {
+    long bad = 0;
+    auto check = [&](uint64_t v) {
+        uint64_t r = 0;   // floor(sqrt(v)), capped
+        while (r < 255 && (r + 1) * (r + 1) <= v) ++r;
+        bad += rk::isqrt_cap255((uint32_t)v) != r;
+    };
+    for (uint64_t v = 0; v < (1u << 17); ++v) check(v);
+    for (uint64_t r = 1; r < 32768; ++r)
+        for (uint64_t v = r * r - 1; v <= r * r + 1; ++v) check(v);
+    check(2ull * 16383 * 16383);
+    check(0x7fffffffu);
+    return bad;
+}
+
+static int emu_edt(const uint8_t *img_in, int h, int w, int mode, int n_waves, int32_t *d2_out, uint8_t *d8_out,
+                   int32_t *cols_out = nullptr) {
     using namespace rk;
     // padded pitches, exact-size allocations; widths divisible by 4 take the dword path
     const int64_t pitch_img = w % 4 == 0 ? w + 4 : w + 1, pitch_g = w % 4 == 0 ? w + 4 : w + 2;
@@ -401,6 +419,8 @@ static int emu_edt(const uint8_t *img_in, int h, int w, int mode, int n_waves, i
                 if (kern == 0) edt_zeros(a);
                 else edt_cols(a);
             }
+    if (cols_out)   // the column pass's plane as it stands in memory
+        for (int y = 0; y < h; ++y) std::memcpy(cols_out + (size_t)y * w, &g[(size_t)y * pitch_g], (size_t)w * 4);
     std::atomic<int> bad{0};
     std::vector<std::thread> th;
     for (int gi = 0; gi < n_waves; ++gi)
@@ -765,6 +785,25 @@ static int emu_decide(int n, int reps, unsigned seed) {
 //   "op conn hval h w image_path mask_path_or_- out_path" on stdin.
 #include <string>
 int main(int argc, char **argv) {
+    if (argc == 2 && std::string(argv[1]) == "root") {
+        const long bad = emu_root();
+        std::printf("differ %ld\n", bad);
+        return bad == 0 ? 0 : 1;
+    }
+    //   kemu cols <h> <w> <image_path> <plane_out>: the column distances between the two passes
+    if (argc == 6 && std::string(argv[1]) == "cols") {
+        const int h = std::atoi(argv[2]), w = std::atoi(argv[3]);
+        std::vector<uint8_t> img((size_t)h * w);
+        std::vector<int32_t> d2((size_t)h * w), cols((size_t)h * w);
+        FILE *f = std::fopen(argv[4], "rb");
+        if (!f || std::fread(img.data(), 1, img.size(), f) != img.size()) return 4;
+        std::fclose(f);
+        const int rc = emu_edt(img.data(), h, w, 0, 2, d2.data(), nullptr, cols.data());
+        f = std::fopen(argv[5], "wb");
+        std::fwrite(cols.data(), 4, cols.size(), f);
+        std::fclose(f);
+        return rc == 0 ? 0 : 1;
+    }
     //   kemu decide <tasks> <runs> <seed>
     if (argc == 5 && std::string(argv[1]) == "decide") {
         const int broken = emu_decide(std::atoi(argv[2]), std::atoi(argv[3]), (unsigned)std::atoi(argv[4]));
