@@ -872,6 +872,20 @@ __device__ __forceinline__ uint16_t *spill_base(const volatile RK_LDS uint32_t *
     return (uint16_t *)(((uint64_t)sp[1] << 32) | (uint64_t)sp[0]);
 }
 
+// Set the wave's spill queue (null: none).  Before the first block is converged:
+// LDS holds whatever an earlier workgroup left in it.
+template <int BH>
+__device__ __forceinline__ void set_spill(Lds<BH> &L, uint16_t *base, uint32_t cap) {
+    if (lane_id() != 0) return;
+    const uint64_t sb = (uint64_t)(uintptr_t)base;
+    volatile RK_LDS uint32_t *sp = L.sp;
+    sp[0] = (uint32_t)sb;
+    sp[1] = (uint32_t)(sb >> 32);
+    sp[2] = base ? cap : 0u;
+    sp[3] = 0u;
+    sp[4] = 0u;
+}
+
 // Push the pixels flagged by `pred` (one per lane) onto the LDS ring of qcap
 // (a power of two) entries.  Returns false (and pushes nothing) if they do not
 // fit: the caller then keeps them aside and hands them to spill() once its
@@ -1435,6 +1449,10 @@ __device__ __forceinline__ bool visit_block(const TaskDev &t, Lds<BH> &L, WaveSt
 template <int BH>
 __global__ __launch_bounds__(64) void dense_pass(TaskTable tt, KArgs a) {
     Lds<BH> L = lds_layout<BH>();
+    // no spill queue: the launch has one per wave of the revisit grid, and this
+    // grid may have more waves (a full queue ends in another dense seed)
+    set_spill(L, nullptr, 0u);
+    __syncthreads();
     const int ln = lane_id();
     const uint32_t total = total_blocks_of(tt);
     WaveStats st;
@@ -1580,15 +1598,7 @@ __device__ __forceinline__ void release_waiters(const KArgs &a, uint32_t ring_ca
 template <int BH>
 __global__ __launch_bounds__(64) void revisit_drain(TaskTable tt, KArgs a) {
     Lds<BH> L = lds_layout<BH>();
-    if (lane_id() == 0) {   // this wave's spill queue (capacity 0: none)
-        const uint64_t sb = (uint64_t)(uintptr_t)(a.spill ? a.spill + (size_t)blockIdx.x * a.spill_cap : nullptr);
-        volatile RK_LDS uint32_t *sp = L.sp;
-        sp[0] = (uint32_t)sb;
-        sp[1] = (uint32_t)(sb >> 32);
-        sp[2] = a.spill ? a.spill_cap : 0u;
-        sp[3] = 0u;
-        sp[4] = 0u;
-    }
+    set_spill(L, a.spill ? a.spill + (size_t)blockIdx.x * a.spill_cap : nullptr, a.spill_cap);
     __syncthreads();
     const int ln = lane_id();
     Work *w = a.work;
