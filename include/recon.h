@@ -128,7 +128,10 @@ typedef struct {
     recon_image image;
     recon_image mask;
     int32_t scan_rounds;   /* per-task tuning: directional pass rounds (0 = context default,
-                              -1 = none, 1..8) */
+                              -1 = none, 1..8).  -1 asks for the queue kernel (see below), and one
+                              task that does takes its whole launch there: the whole recon_batch
+                              call (the tasks of its block height, where heights differ), and
+                              the requests that the serving loop launches with it */
     int32_t queue_capacity;/* per-task tuning: LDS queue entries, a power of two (0 = context
                               default; at most the context's queue_capacity) */
     int32_t h;             /* RECON_OP_HDOME: dome height 1..255; ignored by the others */

@@ -1,10 +1,14 @@
-"""Autotuner for librecon: block rows, LDS queue capacity and scan-pass rounds.
+"""Autotuner for librecon: the kernel, and the queue kernel's block rows and LDS queue capacity.
 
-The knobs change speed, never bytes (the reconstruction is unique).  All three
-travel per task, so one batched call can use a different setting for each size
-bucket: scan rounds and queue capacity inside one launch, block rows (which set
-the kernels' LDS layout) by running each block height's tasks as a launch of
-their own, side by side with the others.
+The knobs change speed, never bytes (the reconstruction is unique).  A task
+that sweeps (scan_rounds of 1 or more) runs on the register-resident kernel,
+which reads neither the number of rounds nor block rows nor queue capacity:
+that is one choice, the default.  With scan_rounds -1 it runs on the queue
+kernel, which the other two steer.  The knobs travel per task, but a batch runs
+on one kernel: a single task that asks for the queue kernel takes the whole
+batch there (queue capacities then differ inside a launch, and the tasks of
+each block height, which sets the kernel's LDS layout, run as a launch of their
+own, side by side with the others).
 
     python -m paper_1209_3332_amd.tune [--out FILE] [--reps N]
 
@@ -30,7 +34,7 @@ DEFAULT_CACHE = os.environ.get("RECON_TUNE_CACHE", os.path.join(HERE, "tune_cach
 
 BLOCK_ROWS = (16, 32, 64)
 QUEUE_CAPACITY = (512, 2048, 8192)
-SCAN_ROUNDS = (-1, 1, 2, 3, 4)   # -1: no sweep on first visits (seed and queue only)
+DEFAULT = {"block_rows": 32, "scan_rounds": 3, "queue_capacity": 2048}   # the register-resident kernel
 # size buckets by tile area (pixels): representative side length of each
 BUCKETS = (("small", 1 << 20, 768), ("medium", 6 << 20, 2048), ("large", 1 << 62, 4096))
 
@@ -88,20 +92,29 @@ def config_for(cache: dict, h: int, w: int, conn: int, arch: str | None = None) 
     """Tuned {block_rows, scan_rounds, queue_capacity} for a tile (defaults if untuned)."""
     entry = cache.get(arch or cache.get("arch", ""), {}) if cache else {}
     return entry.get("%s/conn%d" % (bucket_of(h, w), conn),
-                     {"block_rows": 32, "scan_rounds": 3, "queue_capacity": 2048})
+                     dict(DEFAULT))
+
+
+def candidates() -> list:
+    """Every choice that can run differently, once."""
+    return [dict(DEFAULT)] + [{"block_rows": bh, "scan_rounds": -1, "queue_capacity": qc}
+                              for bh, qc in itertools.product(BLOCK_ROWS, QUEUE_CAPACITY)]
 
 
 def tuned_batch(cache: dict, tasks: list) -> tuple[int, int, list]:
     """Block rows for the context (the choice of the bucket holding most pixels),
     the context's queue capacity (the largest per-task choice: it sizes the LDS
     of every workgroup) and the tasks with their per-task block rows, scan
-    rounds and queue capacity filled in."""
+    rounds and queue capacity filled in.  Unless every task's bucket chose the
+    queue kernel, none of them asks for it (it would take the others there)."""
     weight = {}
     out = []
     qmax = 0
-    for t in tasks:
+    cfgs = [config_for(cache, *t["image"].shape, t.get("conn", 8)) for t in tasks]
+    if any(c["scan_rounds"] != -1 for c in cfgs):
+        cfgs = [dict(DEFAULT) if c["scan_rounds"] == -1 else c for c in cfgs]
+    for t, cfg in zip(tasks, cfgs):
         h, w = t["image"].shape
-        cfg = config_for(cache, h, w, t.get("conn", 8))
         weight[cfg["block_rows"]] = weight.get(cfg["block_rows"], 0) + h * w
         qmax = max(qmax, cfg["queue_capacity"])
         out.append(dict(t, scan_rounds=cfg["scan_rounds"], queue_capacity=cfg["queue_capacity"],
@@ -133,22 +146,21 @@ def tune(reps: int = 3, n_px_target: int = 48 << 20, log=print) -> dict:
             pristine = [torch.from_numpy(j).to(dev) for j, _ in tiles]
             work = [p.clone() for p in pristine]
             best = None
-            for bh, qc in itertools.product(BLOCK_ROWS, QUEUE_CAPACITY):
+            for cfg in candidates():
                 # the context's queue capacity sizes every workgroup's LDS (and so
                 # the occupancy): tune it together with the per-task value
-                with recon.Recon(0, block_rows=bh, queue_capacity=qc, timing=1) as ctx:
-                    for sr in SCAN_ROUNDS:
-                        times = []
-                        for _ in range(reps + 1):
-                            for w_, p_ in zip(work, pristine):
-                                w_.copy_(p_)
-                            ctx.batch([{"op": "dilate", "image": w_, "mask": m_, "conn": conn,
-                                        "scan_rounds": sr, "queue_capacity": qc}
-                                       for w_, m_ in zip(work, masks)])
-                            times.append(ctx.last_stats()["total_ms"])
-                        ms = statistics.median(times[1:])
-                        if best is None or ms < best[0]:
-                            best = (ms, {"block_rows": bh, "scan_rounds": sr, "queue_capacity": qc})
+                with recon.Recon(0, block_rows=cfg["block_rows"], queue_capacity=cfg["queue_capacity"], timing=1) as ctx:
+                    times = []
+                    for _ in range(reps + 1):
+                        for w_, p_ in zip(work, pristine):
+                            w_.copy_(p_)
+                        ctx.batch([{"op": "dilate", "image": w_, "mask": m_, "conn": conn,
+                                    "scan_rounds": cfg["scan_rounds"], "queue_capacity": cfg["queue_capacity"]}
+                                   for w_, m_ in zip(work, masks)])
+                        times.append(ctx.last_stats()["total_ms"])
+                    ms = statistics.median(times[1:])
+                    if best is None or ms < best[0]:
+                        best = (ms, dict(cfg))
             px = sum(m.numel() for m in masks)
             best[1]["ms"] = best[0]
             best[1]["mpx_s"] = px / best[0] / 1e3
