@@ -18,10 +18,11 @@
 // same as the block route's (the reconstruction is unique); the route is only
 // faster.
 //
-// Kernels (one 64-lane wave per workgroup, grid-stride over the blocks of all
-// tasks of the launch, in the scheduler's block numbering: a block of BH x 256
-// pixels is BH / 16 labelling tiles of 16 x 256, or BH rows of 256 pixels),
-// after reset_work has sampled every task's mask (sample_route):
+// Kernels (workgroups of four waves for the first two, of one for the others,
+// grid-stride over the blocks of all tasks of the launch, in the scheduler's
+// block numbering: a block of BH x 256 pixels is BH / 16 labelling tiles of
+// 16 x 256, or units of 4 rows or one of 256 pixels), after reset_work has
+// sampled every task's mask (sample_route):
 //   comp_classify     OR and AND of the nonzero (transformed) mask values of
 //                     every task, into two words per task: the mask is
 //                     two-valued when they are equal (one nonzero value) or the
@@ -246,19 +247,22 @@ __device__ __forceinline__ int32_t comp_root(int32_t *lab, int32_t a, int32_t *e
 // Rows of a unit of the last two kernels: their loads go out together.  Both are
 // bound by the latency of the walks from a pixel to its root: one row at a time,
 // with every entry rewritten as its root's, they took 32-40 us and 14 us for the
-// hole filling of a 2048 x 2048 mask, now 11 and 11.
+// hole filling of a 2048 x 2048 mask, now 11 and 11.  Up to COMP_FEW such units (one
+// per compute unit) a wave takes one row instead: the chip is idle either way, and
+// a lane's walks follow one another (offers of a 5 x 332 mask 14.7 us, 7.9 with
+// a row to a wave; 300 x 300 81 us per call, 66).
 constexpr int COMP_ROWS = 4;
+constexpr uint64_t COMP_FEW = 256;
 
 // The offers.  Only a positive min(J, I) can raise anything, so a pixel without
 // one reads no label: hole filling, whose marker is the image frame, leaves
 // almost all of the label plane alone here.  A lane sums up neighbouring pixels
 // of one component, and the wave the lanes that share the first one's root (one
 // component mostly fills the row), before they reach the root's entry.
-template <int BH>
-__global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
-    if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
+template <int BH, int ROWS>
+__device__ __forceinline__ void offer_units(const TaskTable &tt, const KArgs &a) {
     const int ln = lane_id();
-    constexpr int PER = BH / COMP_ROWS;
+    constexpr int PER = BH / ROWS;
     const uint64_t n = (uint64_t)total_blocks_of(tt) * PER;
     UnitWalk wk;
     for (uint64_t u = blockIdx.x; u < n; u += gridDim.x) {
@@ -267,15 +271,15 @@ __global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
         const TaskDev &t = wk.t;
         if (!on_component_route(a, t, wk.cur)) continue;
         const int lb = (int)(gb - t.block0);
-        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * COMP_ROWS, x0 = (lb % t.nbx) * BW;
+        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * ROWS, x0 = (lb % t.nbx) * BW;
         if (y0 >= t.h) continue;
         const int x = x0 + 4 * ln;
         const int valid = min(4, t.w - x);
         // min(J, I), J the task's initial marker (the caller's for a dilation,
         // else derived here: no marker plane is prepared for a task on this route)
-        uint32_t jm[COMP_ROWS], some = 0;
+        uint32_t jm[ROWS], some = 0;
 #pragma unroll
-        for (int r = 0; r < COMP_ROWS; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             const int y = y0 + r;
             jm[r] = 0;
             if (y < t.h && valid > 0) {
@@ -295,15 +299,15 @@ __global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
                                        __HIP_MEMORY_SCOPE_AGENT);
         };
         if (some != 0u) {
-            int32_t v[COMP_ROWS][4];
+            int32_t v[ROWS][4];
 #pragma unroll
-            for (int r = 0; r < COMP_ROWS; ++r) {
+            for (int r = 0; r < ROWS; ++r) {
                 v[r][0] = v[r][1] = v[r][2] = v[r][3] = 0;
                 if (jm[r] != 0u) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, v[r]);
             }
             int32_t last_v = 0, last_r = 0;   // the lane's pixels mostly share one tile root: one find for them
 #pragma unroll
-            for (int r = 0; r < COMP_ROWS; ++r)
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint32_t off = byte_of(jm[r], k);
@@ -338,14 +342,20 @@ __global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
     }
 }
 
+template <int BH>
+__global__ __launch_bounds__(64) void comp_offer(TaskTable tt, KArgs a) {
+    if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
+    if ((uint64_t)total_blocks_of(tt) * (BH / COMP_ROWS) <= COMP_FEW) offer_units<BH, 1>(tt, a);
+    else offer_units<BH, COMP_ROWS>(tt, a);
+}
+
 // The result: every pixel's root is looked up here (a pixel points at its tile's
 // root, and that one, from the merge or from an earlier look-up, at or near the
 // component's).
-template <int BH>
-__global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
-    if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
+template <int BH, int ROWS>
+__device__ __forceinline__ void write_units(const TaskTable &tt, const KArgs &a) {
     const int ln = lane_id();
-    constexpr int PER = BH / COMP_ROWS;
+    constexpr int PER = BH / ROWS;
     const uint64_t n = (uint64_t)total_blocks_of(tt) * PER;
     UnitWalk wk;
     for (uint64_t u = blockIdx.x; u < n; u += gridDim.x) {
@@ -354,23 +364,23 @@ __global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
         const TaskDev &t = wk.t;
         if (!on_component_route(a, t, wk.cur)) continue;
         const int lb = (int)(gb - t.block0);
-        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * COMP_ROWS, x0 = (lb % t.nbx) * BW;
+        const int y0 = (lb / t.nbx) * BH + (int)(u % PER) * ROWS, x0 = (lb % t.nbx) * BW;
         if (y0 >= t.h) continue;
         if (lb == 0 && u % PER == 0 && ln == 0)   // one count per task that took the route
             __hip_atomic_fetch_add(&a.work->stat_route, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int x = x0 + 4 * ln;
         const int valid = min(4, t.w - x);
         if (valid <= 0) continue;
-        int32_t e[COMP_ROWS][4];
+        int32_t e[ROWS][4];
 #pragma unroll
-        for (int r = 0; r < COMP_ROWS; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             e[r][0] = e[r][1] = e[r][2] = e[r][3] = 0;
             if (y0 + r < t.h) lab_load4(t.lab + (int64_t)(y0 + r) * t.pitch_lab, x, t.w, e[r]);
         }
         int32_t last_e = 0;
         uint32_t last_val = 0;
 #pragma unroll
-        for (int r = 0; r < COMP_ROWS; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             const int y = y0 + r;
             if (y >= t.h) break;
             uint32_t out = 0;
@@ -393,6 +403,13 @@ __global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
                 gstore4(t.img + (int64_t)y * t.pitch_img, x, valid, mapped_result4(t, out, y, x, valid));
         }
     }
+}
+
+template <int BH>
+__global__ __launch_bounds__(64) void comp_write(TaskTable tt, KArgs a) {
+    if (a.work->route_any != seq_of(tt)) return;   // no task of the launch takes the route
+    if ((uint64_t)total_blocks_of(tt) * (BH / COMP_ROWS) <= COMP_FEW) write_units<BH, 1>(tt, a);
+    else write_units<BH, COMP_ROWS>(tt, a);
 }
 
 }  // namespace rk

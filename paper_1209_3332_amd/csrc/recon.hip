@@ -499,7 +499,9 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         // reset_work took already decided every route), then label and
         // reconstruct the two-valued ones (the others' waves exit at once)
         const int bh = kUnitRows[v];
-        const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::COMP_ROWS), 4096));
+        const uint64_t row_units = (uint64_t)nblk * (bh / rk::COMP_ROWS);
+        const int g_rows = (int)std::max<uint64_t>(1, std::min<uint64_t>(
+            row_units <= rk::COMP_FEW ? (uint64_t)nblk * bh : row_units, 4096));
         const int g_tiles = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)nblk * (bh / rk::LT_H), 4096));
         const size_t lds_lab = (size_t)rk::LT_H * rk::LT_W * sizeof(uint32_t);
 #define RK_COMP(K, GRID, THREADS, LDS)                                                                 \
