@@ -576,6 +576,10 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
 // units are full either way and smaller regions trade borders more often.
 // (Strips of 4 rows, or regions of 32 rows, lose everywhere.)
 constexpr uint64_t kSmallRegions = 256;
+// A launch of strips, images of at most rk::STRIP_ROWS rows, does so whatever their
+// length: regions of 128 rows would be mostly empty (two-valued, 2 x 300000: 244 ->
+// 152 us, 176 on the queue kernel), and a flood along a strip is a chain that leaves
+// the chip idle (102 x 161175: 95.9 -> 58.1 ms, 80.5).
 
 // The launch variant of a list of tasks: the register-resident kernel wherever
 // first visits sweep (scan_rounds of every task at least 1, the default); a
@@ -587,8 +591,12 @@ int launch_variant(const recon_config &cfg, const recon_task *tasks, int n) {
         if (tasks[k].scan_rounds < 0 || (tasks[k].scan_rounds == 0 && cfg.scan_rounds == 0))
             return variant_of(cfg.block_rows);
     uint64_t small = 0;
-    for (int k = 0; k < n; ++k) small += (uint64_t)((tasks[k].image.height + 63) / 64) * ((tasks[k].image.width + 255) / 256);
-    return small <= kSmallRegions ? kRegionSmallV : kRegionV;
+    bool strip = true;
+    for (int k = 0; k < n; ++k) {
+        small += (uint64_t)((tasks[k].image.height + 63) / 64) * ((tasks[k].image.width + 255) / 256);
+        strip = strip && tasks[k].image.height <= rk::STRIP_ROWS;
+    }
+    return small <= kSmallRegions || strip ? kRegionSmallV : kRegionV;
 }
 
 // Enqueue one launch sequence for `tasks` on `stream`.  use_graph replays the

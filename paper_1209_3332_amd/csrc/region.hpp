@@ -27,11 +27,11 @@
 // or from the second where a single strip is still changing (a flood that runs
 // along a few rows), each starts with a full row closure of the rows of the strips
 // that changed last, so that long horizontal runs (wide flat areas, corridors)
-// move whole rows at a time.  (A flood along 3 x 300000 pixels, 4-connected, 7.0
-// ms, 23.2 with five passes before every closure and 20.7 on the queue kernel; 100 x
-// 60000 35.3, 38.6, 35.5.  In regions of 64 rows the sixth pass stays the line: a
-// flood along 3 x 30000 6.9 ms against the queue kernel's 8.6, and the sooner
-// closure cost the 512 x 512 tile 2 %.)
+// move whole rows at a time.  (A flood along 3 x 300000 pixels, 4-connected, 4.8
+// ms, 14.3 with five passes before every closure and 20.7 on the queue kernel; 200 x
+// 60000 35.2, 43.6, 41.5.  In regions of 64 rows the sixth pass stays the line for
+// images of more than STRIP_ROWS rows, whose floods seldom keep to a strip: the
+// sooner closure cost the 512 x 512 tile 2 %.)
 //
 // A launch with at most a region per workgroup waits on chains of visits: there
 // each workgroup keeps its region in registers after a visit and waits for the
@@ -65,7 +65,8 @@
 namespace rk {
 
 constexpr int REGION_PAIRS = 8;        // sweep pairs of a visit before its borders are traded
-constexpr int REGION_CLOSURE_PASS = 5; // passes without convergence before rows are closed (1, where a single strip of 16 rows changes)
+constexpr int REGION_CLOSURE_PASS = 5; // passes without convergence before rows are closed (see above for the single strip)
+constexpr int STRIP_ROWS = 192;        // images of at most this many rows are strips (see the launch's choice of regions)
 
 // LDS of a region's workgroup, in 32-bit words
 template <int R, int NW>
@@ -824,6 +825,7 @@ __global__ __launch_bounds__(64 * NW, 4) void region_drain(TaskTable tt, KArgs a
         }
         bool fail = false;
         int stuck_passes = 0;
+        const bool soon = R >= 16 || t.h <= STRIP_ROWS;   // a single strip's change closes its rows in the next pass
         uint32_t carry = first ? 1u : 0u, held_state = first ? ST_R : (ST_V | ST_R), sent = REQ_NONE;
         uint32_t *own = state_word(a, gb);
         for (int pass = 0;; ++pass) {
@@ -844,7 +846,7 @@ __global__ __launch_bounds__(64 * NW, 4) void region_drain(TaskTable tt, KArgs a
             const uint32_t active =
                 region_pass<R, NW>(L, t, g, wv, y0, rows, s, h, seen, dense, carry, loaded, own, requested);
             carry = (active >> wv) & 1u;
-            stuck_passes = !active ? 0 : stuck_passes + (R >= 16 && (active & (active - 1u)) == 0u ? REGION_CLOSURE_PASS : 1);
+            stuck_passes = !active ? 0 : stuck_passes + (soon && (active & (active - 1u)) == 0u ? REGION_CLOSURE_PASS : 1);
             if (ctl[RC_STORED]) {
                 want = wanted_neighbours<R, NW>(L, g, wv, s, h, t.conn);
                 if (want && ln == 0)
