@@ -221,10 +221,10 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// Whether task k takes the component route (component.hpp), as queue_tasks
+// Whether task k takes the component route (component.hpp), as decide_tasks
 // decided: its mask holds at most one nonzero value (two_valued: by the OR and
 // AND of its nonzero mask values that comp_classify left in its route words),
-// and the route pays.  Read only by kernels launched after queue_tasks.
+// and the route pays.  Read only by kernels launched after that.
 __device__ __forceinline__ bool two_valued(const uint32_t *route, int k) {
     const uint32_t o = route[ROUTE_WORDS * k], n = route[ROUTE_WORDS * k + 1];
     return o == 0u || o == n;

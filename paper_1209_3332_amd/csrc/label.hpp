@@ -127,9 +127,9 @@ __device__ __forceinline__ void lds_union(RK_LDS uint32_t *par, uint32_t a, uint
 // second step on they are at the device-coherent level, a trip to memory each: on
 // a long chain the copies in a cache grow old while other waves shorten it, and a
 // walk over them ends far below the root, to go on from there by one g_union
-// minimum per entry (a serpentine of 2995 x 1846 pixels, a leg every 3 rows: merge
-// 189 us with ordinary loads throughout, 31 so; labels of noise, mazes and
-// corridors 4.5 % faster, those of nuclei the same).
+// minimum per entry (labels of a 2995 x 1846 serpentine, a leg every 3 rows: 325 us
+// with ordinary loads throughout, 230 with none and the tiles before, 87 so; of
+// noise, mazes and corridors 4.5 % faster, of nuclei the same).
 __device__ __forceinline__ int32_t g_find(int32_t *lab, int32_t a) {
     const RK_GLOBAL int32_t *l = (const RK_GLOBAL int32_t *)lab;
     for (bool near = true;; near = false) {
