@@ -59,7 +59,12 @@ def percentile(xs, q):
 
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1209_3332_amd", "csrc", f)
                   for f in ("kernels.hpp", "region.hpp", "component.hpp", "label.hpp", "recon.hip")]
-TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "revisit_drain_hbm_traffic.md")
+TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "region_drain_hbm_traffic.md")
+
+
+def visit_kernel(cfg):
+    """The kernel that makes a launch's visits: the queue kernel for tasks without sweeps, else the region kernel."""
+    return "revisit_drain" if cfg.get("scan_rounds", 0) < 0 else "region_drain"
 
 
 def kernel_sha():
@@ -280,29 +285,32 @@ def headline(recon, torch, cfg, marker, mask, binary, steps, warmup, mode):
     ops_of = {"dilate + fill_holes": ("dilate", "fill_holes"), "dilate": ("dilate",), "fill_holes": ("fill_holes",)}
     for name, ts in groups.items():
         st = stats[name]
-        # which operations the launch completed in revisit_drain and which in the
+        # which operations the launch completed in its block visits and which in the
         # component route (the binary fill-holes takes the route; the grey
         # reconstruction the block visits)
         on_route = ("fill_holes",) if st["component_tasks"] == 1 and "fill_holes" in ops_of[name] else ()
         kernels[name] = {"dense_pass_ms": avg(ts, "dense_ms"), "border_seed_ms": avg(ts, "seed_ms"),
-                         "revisit_drain_ms": avg(ts, "drain_ms"), "component_route_ms": avg(ts, "route_ms"),
+                         "drain_kernel": visit_kernel(cfg), "drain_ms": avg(ts, "drain_ms"),
+                         "component_route_ms": avg(ts, "route_ms"),
                          "launch_ms": avg(ts, "total_ms"),
                          "dense_visits": st["dense_visits"], "revisits": st["revisits"], "reruns": st["reruns"],
                          "queue_overflows": st["queue_overflows"], "component_tasks": st["component_tasks"],
-                         "ops_in_revisit_drain": [o for o in ops_of[name] if o not in on_route],
+                         "ops_in_drain": [o for o in ops_of[name] if o not in on_route],
                          "ops_in_component_route": list(on_route)}
     # dominant kernel (by average duration) and its roofline.  Algorithmic bytes
     # per the method's own traffic: 3 B/px for a reconstruction (read the mask,
     # read the marker, write the result), 2 B/px for a fill-holes (read the
     # image, write the result), counted for the operations that kernel
-    # completes.  The bytes a visit schedule moves (3 B/px of a block per
-    # visit, first or later) are reported beside them as per_visit_bytes.
+    # completes.  The bytes a visit schedule of the queue kernel moves (3 B/px of
+    # a block per visit, first or later) are reported beside them as
+    # per_visit_bytes (null for the region kernel, which keeps regions in registers
+    # and stores changed strips).
     bh = cfg.get("block_rows", 32)
+    drain = visit_kernel(cfg)
     cand = []
     for name, kv in kernels.items():
-        cand.append(("revisit_drain (%s)" % name, kv["revisit_drain_ms"],
-                     sum(op_bytes[o] for o in kv["ops_in_revisit_drain"]),
-                     3.0 * bh * 256 * (kv["revisits"] + kv["dense_visits"])))
+        cand.append(("%s (%s)" % (drain, name), kv["drain_ms"], sum(op_bytes[o] for o in kv["ops_in_drain"]),
+                     3.0 * bh * 256 * (kv["revisits"] + kv["dense_visits"]) if drain == "revisit_drain" else None))
         if kv["ops_in_component_route"]:
             cand.append(("component route (%s)" % name, kv["component_route_ms"],
                          sum(op_bytes[o] for o in kv["ops_in_component_route"]), None))
@@ -368,11 +376,11 @@ def next_ops(recon, torch, mask, steps, conn=8, h=20):
         defer_check(("next_ops", op, "parity"), got, *call, rate_path=("next_ops", op, "oracle_single_core_Mpixel_s"),
                     px=mask.size)
         drain = sum(x["drain_ms"] for x in kt) / len(kt)
-        visits = st["dense_visits"] + st["revisits"]
+        moved = (BYTES_DILATE if op == "erode" else BYTES_FILL) * mask.size   # two planes read, or one
         res[op] = {"Mpixel_s": mask.size * steps / wall / 1e6, "ms_per_launch": wall * 1e3 / steps,
-                   "revisit_drain_ms": drain, "launch_ms": sum(x["total_ms"] for x in kt) / len(kt),
+                   "drain_kernel": "region_drain", "drain_ms": drain, "launch_ms": sum(x["total_ms"] for x in kt) / len(kt),
                    "dense_visits": st["dense_visits"], "revisits": st["revisits"],
-                   "revisit_drain_GBs": 3.0 * 32 * 256 * visits / (drain * 1e-3) / 1e9,
+                   "drain_GBs": moved / (drain * 1e-3) / 1e9,
                    "oracle_single_core_Mpixel_s": None, "parity": None}
         log("%s: %.0f Mpixel/s (%.3f ms/launch)" % (op, res[op]["Mpixel_s"], res[op]["ms_per_launch"]))
         del bufs
@@ -492,13 +500,13 @@ def distance(recon, torch, binary, steps, conn=8):
     return res
 
 
-def batch_roofline(name, px, launch_ms):
+def batch_roofline(name, px, launch_ms, drain):
     """Roofline of a batched launch: the method's bytes (3 B/px per reconstruction)
-    over the launch, and the counted HBM bytes of its revisit kernel when the
+    over the launch, and the counted HBM bytes of its kernel `drain` when the
     committed counter summary covers this section on the current kernels."""
     alg = BYTES_DILATE * px
     achieved = alg / (launch_ms * 1e-3) / 1e9
-    traffic = committed_traffic("revisit_drain (%s)" % name)
+    traffic = committed_traffic("%s (%s)" % (drain, name))
     return {"bound": "hbm", "algorithmic_bytes": alg, "launch_ms": launch_ms, "achieved": achieved,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
             "traffic_over_algorithmic": traffic / alg if traffic else None,
@@ -551,7 +559,7 @@ def batched_vs_per_tile(recon, torch, ctx_cfg, n_tiles, size, workers, spiral_si
                           "revisits": st["revisits"], "component_tasks": st["component_tasks"]}
 
         work, res["batched"] = batched(every)
-        res["roofline"] = batch_roofline("64-tile batch", px_of(every), res["batched"]["launch_ms"])
+        res["roofline"] = batch_roofline("64-tile batch", px_of(every), res["batched"]["launch_ms"], visit_kernel(ctx_cfg))
         # a spiral corridor's reconstruction is its mask; nuclei tiles go to the oracle leg
         res["spirals_equal_mask"] = all(torch.equal(work[i], masks[i]) for i in spirals)
         res["parity_checked_tiles"] = [nuclei[j] for j in sorted({0, len(nuclei) // 3, 2 * len(nuclei) // 3,
@@ -642,7 +650,7 @@ def uneven_batched_vs_per_tile(recon, torch, n_tiles, workers, per_tile_legs=Tru
         res["batched"] = {"Mpixel_s": px / wall / 1e6, "ms": wall * 1e3, "launch_ms": st["total_ms"],
                           "queue_overflows": st["queue_overflows"], "queue_spills": st["queue_spills"],
                           "revisits": st["revisits"], "reruns": st["reruns"], "dense_visits": st["dense_visits"]}
-        res["roofline"] = batch_roofline("uneven batch", px, st["total_ms"])
+        res["roofline"] = batch_roofline("uneven batch", px, st["total_ms"], visit_kernel(tuned[0]))
         # parity on a stratified sample: two tiles of every size bucket and connectivity
         strata = {}
         for i, (j, m, c) in enumerate(tiles):
