@@ -75,8 +75,10 @@
  *   serving lanes run up to three).  With four to eight contexts running
  *   4096 x 4096 reconstructions, labellings and distance transforms side by
  *   side, a few runs had a launch given up by its scheduler watchdog or
- *   results that differed, for a cause not found; a caller doing so should
- *   check every launch's outcome (recon_last_stats, recon_enqueue_status).
+ *   results that differed, for a cause not shown (a fault that fits, in the
+ *   clearing of a grown workspace, has been mended since; those runs were
+ *   not repeated); a caller doing so should check every launch's outcome
+ *   (recon_last_stats, recon_enqueue_status).
  */
 #ifndef RECON_H
 #define RECON_H
