@@ -123,8 +123,15 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
             acc_or |= (uint32_t)__shfl_xor((int)acc_or, d);
             acc_and &= (uint32_t)__shfl_xor((int)acc_and, d);
         }
+        uint32_t *wo = a.route + ROUTE_WORDS * acc_k, *wa = wo + 1;
         if (ln == 0 && ((acc_or & ~seen_or) | (seen_and & ~acc_and)) != 0u) {
-            uint32_t *wo = a.route + ROUTE_WORDS * acc_k, *wa = wo + 1;
+            // looked up again: where the samples met no foreground, every wave's copies
+            // still say so, and one word would take as many atomics as there are waves
+            // (hole filling of a 4096 x 4096 checkerboard 240 us, 142 so)
+            seen_or = __hip_atomic_load(wo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            seen_and = __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (ln == 0 && ((acc_or & ~seen_or) | (seen_and & ~acc_and)) != 0u) {
             if ((acc_or & ~seen_or) != 0u) __hip_atomic_fetch_or(wo, acc_or, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((seen_and & ~acc_and) != 0u) __hip_atomic_fetch_and(wa, acc_and, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // (read back after both: of the waves that make a task grey together, the last one sees it)
