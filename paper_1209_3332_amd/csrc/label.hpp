@@ -121,25 +121,20 @@ __device__ __forceinline__ void lds_union(RK_LDS uint32_t *par, uint32_t a, uint
 // grandparent (an atomic minimum: a parent always has the smaller id, so the
 // entry only moves up its own tree, whatever other waves write meanwhile).
 // Without it, a component spanning many tiles (a background, a corridor)
-// builds chains as long as the tiles it crosses.  The first step's loads are
-// ordinary ones: an entry only ever moves up its tree, so a copy that a cache
-// holds from before still names an ancestor, mostly the root at once.  From the
-// second step on they are at the device-coherent level, a trip to memory each: on
-// a long chain the copies in a cache grow old while other waves shorten it, and a
-// walk over them ends far below the root, to go on from there by one g_union
-// minimum per entry (labels of a 2995 x 1846 serpentine, a leg every 3 rows: 325 us
-// with ordinary loads throughout, 230 with none and the tiles before, 87 so; of
-// noise, mazes and corridors 4.5 % faster, of nuclei the same).
+// builds chains as long as the tiles it crosses.  The loads are at the
+// device-coherent level, a trip to memory each: over copies that a cache holds from
+// before other waves linked or shortened a chain, a walk ends far below the root, and
+// goes on from there by one g_union minimum per entry (labels of a 2995 x 1846
+// serpentine, a leg every 3 rows: 325 us with ordinary loads, 110 so; of a 5000 x 64
+// spiral 285 us with ordinary loads in the first step alone, 155 so; hole filling
+// of a 2048 x 2048 nuclei mask 96 and 97.5).
 __device__ __forceinline__ int32_t g_find(int32_t *lab, int32_t a) {
-    const RK_GLOBAL int32_t *l = (const RK_GLOBAL int32_t *)lab;
-    for (bool near = true;; near = false) {
-        auto entry = [&](int32_t n) -> int32_t {
-            return near ? l[n - 1] : __hip_atomic_load((RK_GLOBAL int32_t *)(lab + (n - 1)), __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        };
-        const int32_t p = entry(a);
+    while (true) {
+        const int32_t p = __hip_atomic_load((RK_GLOBAL int32_t *)(lab + (a - 1)), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
         if (p == a) return a;
-        const int32_t gp = entry(p);
+        const int32_t gp = __hip_atomic_load((RK_GLOBAL int32_t *)(lab + (p - 1)), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
         if (gp == p) return p;
         __hip_atomic_fetch_min((RK_GLOBAL int32_t *)(lab + (a - 1)), gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         a = gp;

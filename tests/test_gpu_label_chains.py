@@ -19,7 +19,7 @@ def _masks(h, w):
 
 
 @pytest.mark.parametrize("conn", [8, 4])
-@pytest.mark.parametrize("h,w", [(300, 517), (1025, 1030), (2995, 1846)])
+@pytest.mark.parametrize("h,w", [(300, 517), (1025, 1030), (2995, 1846), (5000, 64), (61, 5003)])
 def test_chains(oracle_mod, h, w, conn):
     import torch
     import paper_1209_3332_amd as lib
