@@ -256,7 +256,7 @@ __device__ __forceinline__ int32_t comp_root(int32_t *lab, int32_t a, int32_t *e
 // with every entry rewritten as its root's, they took 32-40 us and 14 us for the
 // hole filling of a 2048 x 2048 mask, now 11 and 11.  Up to COMP_FEW such units (one
 // per compute unit) a wave takes one row instead: the chip is idle either way, and
-// a lane's walks follow one another (offers of a 5 x 332 mask 14.7 us, 7.9 with
+// a lane's walks follow one another (offers of a 3 x 2817 mask 14.7 us, 7.9 with
 // a row to a wave; 300 x 300 81 us per call, 66).
 constexpr int COMP_ROWS = 4;
 constexpr uint64_t COMP_FEW = 256;
