@@ -100,6 +100,12 @@ struct UnitWalk {
 // 2048 x 2048 mask, 21 with 32 rows to a wave and a wave to a workgroup.
 constexpr int CLASS_WAVES = 4;
 
+// Whether a task's words, read while waves add to them, show two different nonzero
+// values.  The words change one after the other: an OR beside the AND's identity is
+// one wave's on its way, of a mask that may hold a single value.  (The AND of two
+// different values is never the identity.)
+__device__ __forceinline__ bool shows_grey(uint32_t o, uint32_t n) { return o != 0u && n != 0xffu && o != n; }
+
 template <int BH>
 __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, KArgs a) {
     if (a.work->classify_skip == seq_of(tt)) return;   // the samples decided every route
@@ -139,7 +145,7 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
             const uint32_t na = __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // this task is grey (any writer, same value; a plain load first so
             // that a line already holding it is not written again by every wave)
-            if (no != 0u && no != na && a.work->has_grey != seq)
+            if (shows_grey(no, na) && a.work->has_grey != seq)
                 __hip_atomic_store(&a.work->has_grey, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         acc_or = 0;
@@ -157,7 +163,7 @@ __global__ __launch_bounds__(64 * CLASS_WAVES) void comp_classify(TaskTable tt, 
         const uint32_t *rw = a.route + ROUTE_WORDS * wk.cur;
         seen_or = rw[0];
         seen_and = rw[1];
-        if (uniform(seen_or != 0u && seen_or != seen_and ? 1 : 0)) continue;
+        if (uniform(shows_grey(seen_or, seen_and) ? 1 : 0)) continue;
         // a thick mask beside grey work keeps the block route whatever its
         // values (decide_tasks), so it is not read either
         if (uniform(a.route_policy != 1 && rw[4] == 0u && a.work->has_grey == seq ? 1 : 0)) continue;

@@ -779,6 +779,46 @@ static int emu_decide(int n, int reps, unsigned seed) {
     return broken;
 }
 
+// comp_classify of one mask, its route words as a wave finds them that comes between
+// another wave's two atomics (the OR is there, the AND still the identity): the words
+// it leaves must show every value of the mask.
+static int emu_classify(const uint8_t *mask, int h, int w, uint32_t o0, uint32_t n0, uint32_t *o, uint32_t *n) {
+    using namespace rk;
+    std::vector<uint8_t> img(mask, mask + (size_t)h * w), marker((size_t)h * w);
+    int32_t plane = 0;
+    TaskTable tt{};
+    TaskDev &t = tt.inl[0];
+    t.h = h;
+    t.w = w;
+    t.conn = 8;
+    t.nby = (h + 31) / 32;
+    t.nbx = (w + BW - 1) / BW;
+    t.i = img.data();
+    t.pitch_i = w;
+    t.j = marker.data();
+    t.pitch_j = w;
+    t.aligned = w % 4 == 0;
+    t.lab = &plane;
+    tt.n_inline = 1;
+    tt.total_inline = (uint32_t)(t.nby * t.nbx);
+    tt.seq_inline = 7;
+    Work work{};
+    std::vector<uint32_t> route(ROUTE_WORDS, 0u), pend(1), done(1);
+    route[0] = o0;
+    route[1] = n0;
+    route[4] = 1u;
+    KArgs a{};
+    a.work = &work;
+    a.route = route.data();
+    a.route_policy = 1;
+    a.tile_pending = pend.data();
+    a.tile_done = done.data();
+    const int bad = workgroups(3, CLASS_WAVES, 16, [&] { comp_classify<32>(tt, a); });
+    *o = route[0];
+    *n = route[1];
+    return bad;
+}
+
 #ifdef KEMU_MAIN
 // Stand-alone driver (lets the sanitizer runtime link into the executable):
 //   kemu <bh> <qcap> <scan_rounds> <waves> <watchdog_s> <n> then n lines of
@@ -803,6 +843,18 @@ int main(int argc, char **argv) {
         std::fwrite(cols.data(), 4, cols.size(), f);
         std::fclose(f);
         return rc == 0 ? 0 : 1;
+    }
+    //   kemu classify <h> <w> <image_path> <or> <and>: the words after the classification
+    if (argc == 7 && std::string(argv[1]) == "classify") {
+        const int h = std::atoi(argv[2]), w = std::atoi(argv[3]);
+        std::vector<uint8_t> img((size_t)h * w);
+        FILE *f = std::fopen(argv[4], "rb");
+        if (!f || std::fread(img.data(), 1, img.size(), f) != img.size()) return 4;
+        std::fclose(f);
+        uint32_t o = 0, n = 0;
+        const int bad = emu_classify(img.data(), h, w, (uint32_t)std::atoi(argv[5]), (uint32_t)std::atoi(argv[6]), &o, &n);
+        std::printf("or %u and %u\n", o, n);
+        return bad == 0 ? 0 : 1;
     }
     //   kemu decide <tasks> <runs> <seed>
     if (argc == 5 && std::string(argv[1]) == "decide") {
