@@ -251,6 +251,15 @@ void free_workspace(recon_ctx *c) {
     c->cap_tasks = c->cap_blocks = c->cap_scratch = 0;
 }
 
+void drop_capture_streams(recon_ctx *c) {
+    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    if (c->aux_stream) (void)hipStreamDestroy(c->aux_stream);
+    if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
+    if (c->ev_join) (void)hipEventDestroy(c->ev_join);
+    c->cap_stream = c->aux_stream = nullptr;
+    c->ev_fork = c->ev_join = nullptr;
+}
+
 void drop_graphs(recon_ctx *c) {
     for (int v = 0; v < kLaunchVariants; ++v) {
         if (c->graph[v]) (void)hipGraphExecDestroy(c->graph[v]);
@@ -259,13 +268,22 @@ void drop_graphs(recon_ctx *c) {
     }
 }
 
+// A device synchronisation fails, on any thread, while any stream of the process is
+// being captured, and breaks that capture (also one of thread-local mode: measured
+// on ROCm 7.0).  So one context's growth and another's capture, on threads of
+// their own (a serving loop's worker among them), take turns.
+std::mutex g_capture_mu;
+
 // Grow the workspace to hold n_tasks tasks, n_blocks blocks and `area_bytes`
 // bytes of scratch planes, for a launch on `stream`.  Growing synchronises the
 // device and drops the captured graphs (they hold the old pointers).
 int ensure_capacity(recon_ctx *c, size_t n_tasks, size_t n_blocks, size_t area_bytes, hipStream_t stream) {
     if (n_tasks <= c->cap_tasks && n_blocks <= c->cap_blocks && area_bytes <= c->cap_scratch)
         return RECON_OK;
-    HIP_TRY(hipDeviceSynchronize());
+    {
+        std::lock_guard<std::mutex> lk(g_capture_mu);
+        HIP_TRY(hipDeviceSynchronize());
+    }
     drop_graphs(c);
     const size_t nt = std::max(c->cap_tasks, std::max<size_t>(n_tasks, 64));
     const size_t nb = std::max(c->cap_blocks, std::max<size_t>(n_blocks, 4096));
@@ -527,6 +545,12 @@ int enqueue_kernels(recon_ctx *c, const Workspace &ws, int v, const rk::TaskTabl
         if (dynamic_sizes) {
             HIP_TRY(hipEventRecord(c->ev_fork, s));
             HIP_TRY(hipStreamWaitEvent(c->aux_stream, c->ev_fork, 0));
+            // On a stream whose capture was broken, from another thread, both calls
+            // above succeed and the fork is no part of a capture: what it is sent
+            // would run now, on a task table that no one copied.
+            hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+            HIP_TRY(hipStreamIsCapturing(c->aux_stream, &st));
+            if (st != hipStreamCaptureStatusActive) return fail(RECON_EDEVICE, "graph capture was broken");
             d = c->aux_stream;
         }
         RK_COMP(comp_label_local, g_tiles, 64 * rk::LT_WAVES, lds_lab);
@@ -655,29 +679,41 @@ int run_tasks(recon_ctx *c, const recon_task *tasks, int n, hipStream_t stream, 
     }
     const uint32_t table_bytes = (uint32_t)(sizeof(BatchHdr) + table.size() * sizeof(rk::TaskDev));
 
-    if (use_graph) {
-        if (!c->graph[v] || c->graph_cap_blocks[v] != c->cap_blocks || c->graph_cap_tasks[v] != c->cap_tasks ||
-            c->graph_cap_scratch[v] != c->cap_scratch) {
-            if (c->graph[v]) (void)hipGraphExecDestroy(c->graph[v]);
-            c->graph[v] = nullptr;
+    if (use_graph && (!c->graph[v] || c->graph_cap_blocks[v] != c->cap_blocks || c->graph_cap_tasks[v] != c->cap_tasks ||
+                      c->graph_cap_scratch[v] != c->cap_scratch)) {
+        if (c->graph[v]) (void)hipGraphExecDestroy(c->graph[v]);
+        c->graph[v] = nullptr;
+        hipGraph_t g = nullptr;
+        hipError_t e;
+        {
+            std::lock_guard<std::mutex> lk(g_capture_mu);
             if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-            hipGraph_t g = nullptr;
             HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
             const uint32_t max_bytes = (uint32_t)(sizeof(BatchHdr) + c->cap_tasks * sizeof(rk::TaskDev));
             hipLaunchKernelGGL(rk::copy_table, dim3(16), dim3(256), 0, c->cap_stream, c->h_table, c->d_table,
                                max_bytes);
             rc = enqueue_kernels(c, ctx_workspace(c), v, tt, total_blocks, (uint32_t)n, true, with_route, true,
                                  c->cap_stream);
-            hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
-            if (rc) return rc;
-            if (e != hipSuccess) return fail(RECON_EDEVICE, "graph capture failed: %s", hipGetErrorString(e));
+            e = hipStreamEndCapture(c->cap_stream, &g);
+            if (rc != RECON_OK || e != hipSuccess) drop_capture_streams(c);   // (they would stay invalid)
+        }
+        if (rc == RECON_OK && e == hipSuccess) {
             e = hipGraphInstantiate(&c->graph[v], g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return fail(RECON_EDEVICE, "graph instantiate failed: %s", hipGetErrorString(e));
             c->graph_cap_blocks[v] = c->cap_blocks;
             c->graph_cap_tasks[v] = c->cap_tasks;
             c->graph_cap_scratch[v] = c->cap_scratch;
+        } else {
+            // the capture was broken from outside (another thread of the caller's
+            // synchronised the device): this launch goes out kernel by kernel, and
+            // the next one captures anew
+            if (g) (void)hipGraphDestroy(g);
+            (void)hipGetLastError();
+            use_graph = false;
         }
+    }
+    if (use_graph) {
         hipEvent_t *tev = c->tev[c->launches % kTimingRing];
         if (c->cfg.timing) HIP_TRY(hipEventRecord(tev[5], stream));
         HIP_TRY(hipGraphLaunch(c->graph[v], stream));
@@ -1123,10 +1159,7 @@ int recon_destroy(recon_ctx *ctx) {
     for (auto &set : ctx->tev)
         for (auto &ev : set)
             if (ev) (void)hipEventDestroy(ev);
-    if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
-    if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
-    if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
-    if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
+    drop_capture_streams(ctx);
     for (int v = 0; v < kVariants; ++v) {
         if (ctx->shape_ctx[v]) (void)recon_destroy(ctx->shape_ctx[v]);
         if (ctx->shape_stream[v]) (void)hipStreamDestroy(ctx->shape_stream[v]);
